@@ -143,7 +143,7 @@ typedef struct {
 /* Device bytes the caller provides. */
 typedef struct {
     size_t model;        /* fd_create_model's buffer */
-    size_t state;        /* fd_create_state's buffer (two time levels) */
+    size_t state;        /* fd_create_state's buffer (two time levels; 2D FP32 grids: four) */
     size_t checkpoints;  /* fd_run_shot's checkpoint buffer for (nt, ckpt_every) */
     size_t adjoint_work; /* fd_adjoint_gradient's work buffer for ckpt_every */
     size_t routines_work; /* fd_step_routines' work buffer (ndim FP32 fields) */
@@ -180,7 +180,12 @@ fd_status fd_destroy_model(fd_model *model);
  * WaveSimulator, Section 7) to `state_buf` (device, >= fd_sizes.state
  * bytes, 256-byte aligned, owned by the caller and borrowed until
  * fd_destroy_state): the device-resident container of Section 5 (Start and
- * stop).  Host-only; call fd_begin_shot (or fd_set_wavefield) before
+ * stop).  On 2D FP32 grids fd_sizes.state counts a second pair of levels,
+ * which the calls that take many steps (fd_run_shot, fd_run_shots, recorded
+ * shots, fd_step_batch) use to take several steps per launch; a buffer without
+ * it (two levels and the 1.25 KiB of bookkeeping, rounded up to 256 bytes) is
+ * accepted too, and then every step is a launch of its own, with the same
+ * bits.  Host-only; call fd_begin_shot (or fd_set_wavefield) before
  * stepping.  Errors: FD_ERR_INVALID_ARG for NULL arguments, a short or
  * misaligned buffer; FD_ERR_OUT_OF_MEMORY if the host handle cannot be
  * allocated. */
@@ -278,9 +283,9 @@ fd_status fd_rtm_image(const fd_model *model, const fd_shot *shot, const float *
 
 /* Several shots on one model at once (the shots of one survey: a
  * gradient or an image sums over them).  `count` entries in each array;
- * all shots share nt.  In 2D with FP32 storage every time step of all the
- * shots is one launch of the batched step kernel (groups of FD_BATCH_MAX),
- * which keeps the device full on grids too small to fill it alone; otherwise
+ * all shots share nt.  In 2D with FP32 storage the shots share every launch
+ * (groups of FD_BATCH_MAX), which keeps the device full on grids too small
+ * to fill it alone; otherwise
  * the shots run one after another.  Per shot, the results are those of the
  * single-shot call, bit for bit:
  *   fd_run_shots               = fd_run_shot on each (states[i], shots[i],
@@ -373,9 +378,9 @@ typedef struct {
     float *traces;
 } fd_batch_item;
 
-/* Advances every item by up to `nsteps` steps with ONE kernel launch per
- * step covering all items (continuous batching of shots on grids of
- * different sizes).  An item stops at its last step; items[i].n is updated
+/* Advances every item by up to `nsteps` steps with kernel launches that
+ * each cover all items, one or several steps at a time (continuous batching
+ * of shots on grids of different sizes).  An item stops at its last step; items[i].n is updated
  * (host) to the next step of each item.  Results equal fd_step on each
  * item alone, bit for bit.  2D, FP32 storage, count <= FD_BATCH_MAX. */
 fd_status fd_step_batch(fd_batch_item *items, int32_t count, int32_t nsteps, void *stream);

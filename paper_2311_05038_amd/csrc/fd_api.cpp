@@ -27,7 +27,7 @@ fd_status hip_fail(hipError_t e, const char *what)
 fd_status do_begin(const fd_model *m, fd_state *st, const fd_shot *s, hipStream_t stream)
 {
     const Layout &L = m->L;
-    hipError_t e = fdk::launch_fill_u32(st->base, L.state_bytes / 4, 0u, stream);
+    hipError_t e = fdk::launch_fill_u32(st->base, L.state_least / 4, 0u, stream);
     if (e != hipSuccess) return hip_fail(e, "fd_begin_shot fill");
     // a z-slab adds the source only on its own planes
     if (s->src_z >= L.z0 && s->src_z < L.z0 + L.nz) {
@@ -55,6 +55,234 @@ fd_status do_step(const fd_model *m, fd_state *st, const fd_shot *s, int64_t n, 
     hipError_t e = fdk::launch_step(a, m->L.ndim, m->L.storage, fdk::kFwd, stream);
     if (e != hipSuccess) return hip_fail(e, "step kernel launch");
     st->next = n + 1;
+    return FD_OK;
+}
+
+// ---- several 2D FP32 steps per launch --------------------------------------
+
+// How a run of steps is cut into launches of several steps each: `steps` at
+// most per launch, for the least modelled time over the run.
+struct MultiPlan {
+    int steps;   // 0: no shape fits, or single steps are not slower
+};
+
+// A single step's time on `cells` padded cells, us (256^2 4.5, 1024^2 7.4,
+// 2048 x 4096 22): the launch, or the fields' 16 bytes per cell.
+double single_us(double cells) { return std::max(4.5, 2.2 + cells * 2.4e-6); }
+
+// pairs: launches come in pairs that start and end on the same buffers, so a
+// run is cut into whole pairs of `steps` and a rest of one pair (or of one or
+// two single steps).  Otherwise launches follow one another freely.
+MultiPlan plan_multi(const fdk::MultiGrid *grids, int count, int64_t run, bool pairs)
+{
+    double cells = 0.0;
+    for (int i = 0; i < count; ++i) cells += (double)grids[i].nz * grids[i].px;
+    MultiPlan best{0};
+    double best_us = pairs ? (double)run * single_us(cells) : 1e300;
+    double us[fdk::kMultiSteps + 1] = {0.0};
+    for (int k = 1; k <= fdk::kMultiSteps; ++k)
+        if (fdk::multi2d_shape(grids, count, k, &us[k]) < 0) us[k] = 1e300;
+    for (int k = 1; k <= fdk::kMultiSteps && k <= run; ++k) {
+        double t;
+        if (pairs) {
+            const int64_t rest = run % (2 * k);
+            t = (double)(run / (2 * k)) * 2.0 * us[k];
+            t += rest <= 2 ? (double)rest * single_us(cells) : us[(rest + 1) / 2] + us[rest / 2];
+        } else {
+            const int64_t n = (run + k - 1) / k;
+            t = (double)n * us[(run + n - 1) / n];
+        }
+        if (t < best_us) {
+            best_us = t;
+            best.steps = k;
+        }
+    }
+    return best;
+}
+
+fdk::MultiArgs multi_args(const fd_model *m, const fd_shot *s, int64_t n, int steps)
+{
+    const StepArgs a = base_args(m, s);
+    fdk::MultiArgs o{};
+    o.c = a.c;
+    o.gz = a.gz;
+    o.gx = a.gx;
+    o.wavelet = a.wavelet;
+    o.nz = a.nz;
+    o.nx = a.nx;
+    o.px = a.px;
+    o.sz = a.sz;
+    o.sx = a.sx;
+    o.amp = a.amp;
+    o.n = n;
+    o.nt = a.nt;
+    o.rz0 = a.rec.z0;
+    o.rx0 = a.rec.x0;
+    o.rnz = a.rec.nz;
+    o.rnx = a.rec.nx;
+    o.rdz = a.rec.dz;
+    o.rdx = a.rec.dx;
+    o.rec_stride = nrec_of(s);
+    o.steps = steps;
+    return o;
+}
+
+// A shot in flight: up to FD_BATCH_MAX of them advance together.
+struct Flight {
+    const fd_model *m;
+    fd_state *st;
+    const fd_shot *shot;
+    int64_t n, end;   // next step, step to stop at
+    float *traces;    // [nt][nrec] or null
+    float *keep;      // where the levels at step n go (a checkpoint slot), or null
+};
+
+fd_status keep_levels(const Flight &f, hipStream_t s)
+{
+    const size_t bytes = f.m->L.field;
+    hipError_t e = hipMemcpyAsync(f.keep, f.st->buf[f.n & 1], bytes, hipMemcpyDeviceToDevice, s);
+    if (e == hipSuccess)
+        e = hipMemcpyAsync((char *)f.keep + bytes, f.st->buf[(f.n + 1) & 1], bytes, hipMemcpyDeviceToDevice, s);
+    return e == hipSuccess ? FD_OK : hip_fail(e, "checkpoint copy");
+}
+
+// Steps every flight to its end.  Launches of several steps come in pairs:
+// the first writes the state's second pair of levels, the next one writes
+// back, so that after a pair (and so after every call) level n is in
+// buf[n & 1] again, as single steps leave it.  Same bits either way.
+fd_status advance(Flight *f, int count, hipStream_t s)
+{
+    int64_t run = 0;
+    bool paired = true;
+    fdk::MultiGrid grids[FD_BATCH_MAX];
+    for (int i = 0; i < count; ++i) {
+        run = std::max(run, f[i].end - f[i].n);
+        paired = paired && f[i].st->pair[0] != nullptr;
+        grids[i] = fdk::MultiGrid{(int)f[i].m->L.nz, f[i].m->L.px};
+    }
+    const int steps = paired && run > 2 ? plan_multi(grids, count, run, true).steps : 0;
+    while (run > 0) {
+        if (steps > 0 && run > 2) {
+            for (int half = 0; half < 2; ++half) {
+                fdk::MultiArgs it[FD_BATCH_MAX];
+                int k = 0;
+                for (int i = 0; i < count; ++i) {
+                    const int64_t r = std::min<int64_t>(f[i].end - f[i].n, 2 * steps);
+                    if (r <= 0) continue;
+                    // the second half takes the smaller part of what is left
+                    const int64_t first = (r + 1) / 2, nf = half == 0 ? f[i].n : f[i].n + first;
+                    fdk::MultiArgs a = multi_args(f[i].m, f[i].shot, nf, (int)(half == 0 ? first : r - first));
+                    float *b[2] = {(float *)f[i].st->buf[0], (float *)f[i].st->buf[1]};
+                    if (half == 0) {
+                        a.cur = b[nf & 1];
+                        a.prev = b[(nf + 1) & 1];
+                        a.out1 = f[i].st->pair[0];
+                        a.out0 = f[i].st->pair[1];
+                        if (f[i].keep) {
+                            a.keep1 = f[i].keep;
+                            a.keep0 = (float *)((char *)f[i].keep + f[i].m->L.field);
+                        }
+                    } else {
+                        a.cur = f[i].st->pair[0];
+                        a.prev = f[i].st->pair[1];
+                        a.out1 = b[(f[i].n + r) & 1];
+                        a.out0 = b[(f[i].n + r + 1) & 1];
+                    }
+                    if (f[i].traces && nrec_of(f[i].shot) > 0)
+                        a.trace = f[i].traces + (size_t)nf * (size_t)nrec_of(f[i].shot);
+                    it[k++] = a;
+                }
+                const hipError_t e = fdk::launch_multi2d(it, k, fdk::kFwd, s);
+                if (e != hipSuccess) return hip_fail(e, "multi-step launch");
+            }
+            for (int i = 0; i < count; ++i) {
+                const int64_t r = std::min<int64_t>(f[i].end - f[i].n, 2 * steps);
+                if (r <= 0) continue;
+                f[i].n += r;
+                f[i].keep = nullptr;
+                f[i].st->next = f[i].n;
+            }
+            run -= 2 * steps;
+        } else {
+            fdk::Batch2D b;
+            b.count = 0;
+            for (int i = 0; i < count; ++i) {
+                if (f[i].n >= f[i].end) continue;
+                if (f[i].keep) {
+                    const fd_status st = keep_levels(f[i], s);
+                    if (st != FD_OK) return st;
+                    f[i].keep = nullptr;
+                }
+                if (count == 1) {
+                    const int64_t nrec = nrec_of(f[i].shot);
+                    const fd_status st = do_step(f[i].m, f[i].st, f[i].shot, f[i].n,
+                                                 f[i].traces ? f[i].traces + (size_t)f[i].n * (size_t)nrec : nullptr, s);
+                    if (st != FD_OK) return st;
+                } else {
+                    StepArgs a = base_args(f[i].m, f[i].shot);
+                    a.cur = f[i].st->buf[f[i].n & 1];
+                    a.prev = f[i].st->buf[(f[i].n + 1) & 1];
+                    a.n = f[i].n;
+                    const int64_t nrec = nrec_of(f[i].shot);
+                    a.trace_row = (f[i].traces && nrec > 0) ? f[i].traces + (size_t)f[i].n * (size_t)nrec : nullptr;
+                    a.meta = f[i].st->meta;
+                    b.it[b.count++] = a;
+                }
+            }
+            if (count > 1) {
+                const hipError_t e = fdk::launch_step_batch2d(b, s);
+                if (e != hipSuccess) return hip_fail(e, "batched step launch");
+            }
+            for (int i = 0; i < count; ++i)
+                if (f[i].n < f[i].end) f[i].st->next = ++f[i].n;
+            run -= 1;
+        }
+    }
+    return FD_OK;
+}
+
+// Shots of one 2D FP32 model after do_begin: steps 0 .. nt-1 with the
+// checkpoints before steps 0, K, 2K, ... (ckpt may be null) and the traces.
+fd_status run_steps(const fd_model *m, fd_state *const *states, const fd_shot *const *shots, int32_t count,
+                    float *const *traces, void *const *ckpt, int32_t every, hipStream_t s)
+{
+    const int64_t nt = shots[0]->nt;
+    bool any = false;
+    for (int32_t i = 0; ckpt && i < count; ++i) any = any || ckpt[i];
+    const int64_t stride = any ? every : nt;
+    for (int64_t n = 0; n < nt; n += stride) {
+        for (int32_t i0 = 0; i0 < count; i0 += FD_BATCH_MAX) {
+            Flight f[FD_BATCH_MAX];
+            int k = 0;
+            for (int32_t i = i0; i < std::min<int32_t>(count, i0 + FD_BATCH_MAX); ++i) {
+                char *slot = ckpt ? (char *)ckpt[i] : nullptr;
+                if (slot) slot += (size_t)(n / stride) * ckpt_slot_bytes(m->L);
+                f[k++] = Flight{m, states[i], shots[i], n, std::min(nt, n + stride), traces ? traces[i] : nullptr,
+                                (float *)slot};
+            }
+            const fd_status st = advance(f, k, s);
+            if (st != FD_OK) return st;
+        }
+    }
+    return FD_OK;
+}
+
+// The same for one shot of any model.
+fd_status shot_steps(const fd_model *m, fd_state *st, const fd_shot *shot, float *traces, void *ckpt,
+                     int32_t every, hipStream_t s)
+{
+    const Layout &L = m->L;
+    if (L.ndim == 2 && L.storage == FD_F32) return run_steps(m, &st, &shot, 1, &traces, &ckpt, every, s);
+    const int64_t nrec = nrec_of(shot);
+    for (int64_t n = 0; n < shot->nt; ++n) {
+        if (ckpt && n % every == 0) {
+            char *slot = (char *)ckpt + (size_t)(n / every) * ckpt_slot_bytes(L);
+            const fd_status e = keep_levels(Flight{m, st, shot, n, shot->nt, nullptr, (float *)slot}, s);
+            if (e != FD_OK) return e;
+        }
+        const fd_status e = do_step(m, st, shot, n, traces ? traces + (size_t)n * (size_t)nrec : nullptr, s);
+        if (e != FD_OK) return e;
+    }
     return FD_OK;
 }
 
@@ -172,6 +400,8 @@ fd_status fd_create_model(const fd_grid *grid, const float *velocity, void *mode
         (void)fdk::routines_scratch(s, &area);
         StepArgs a = base_args(m, nullptr, nullptr);
         fdk::plan_tiles(a, L.ndim, L.storage, false);
+        const fdk::MultiGrid mg{(int)L.nz, L.px};
+        if (L.ndim == 2) (void)fdk::multi2d_shape(&mg, 1, 1, nullptr);   // the CU count
         (void)hipGetLastError();
     }
     *out = m;
@@ -187,9 +417,9 @@ fd_status fd_destroy_model(fd_model *model)
 fd_status fd_create_state(const fd_model *model, void *state_buf, size_t state_bytes, fd_state **out)
 {
     if (!model || !state_buf || !out) return fail(FD_ERR_INVALID_ARG, "NULL model, buffer or out");
-    if (state_bytes < model->L.state_bytes)
+    if (state_bytes < model->L.state_least)
         return fail(FD_ERR_INVALID_ARG, "state buffer too small (%zu < %zu bytes)", state_bytes,
-                    model->L.state_bytes);
+                    model->L.state_least);
     if ((uintptr_t)state_buf % kAlign) return fail(FD_ERR_INVALID_ARG, "state buffer must be 256-byte aligned");
     fd_state *st = new (std::nothrow) fd_state;
     if (!st) return fail(FD_ERR_OUT_OF_MEMORY, "host allocation failed");
@@ -197,6 +427,9 @@ fd_status fd_create_state(const fd_model *model, void *state_buf, size_t state_b
     st->base = state_buf;
     st->buf[0] = (char *)state_buf + model->L.ghost;
     st->buf[1] = (char *)state_buf + model->L.field + model->L.ghost;
+    const bool paired = model->L.pair_off != 0 && state_bytes >= model->L.state_bytes;
+    for (int k = 0; k < 2; ++k)
+        st->pair[k] = paired ? (float *)((char *)state_buf + model->L.pair_off + k * model->L.field) : nullptr;
     st->meta = (int32_t *)((char *)state_buf + model->L.meta_off);
     st->next = -1;
     *out = st;
@@ -254,20 +487,8 @@ fd_status fd_run_shot(const fd_model *model, fd_state *state, const fd_shot *sho
     hipStream_t s = (hipStream_t)stream;
     st = do_begin(model, state, shot, s);
     if (st != FD_OK) return st;
-    const int64_t nrec = nrec_of(shot);
-    for (int64_t n = 0; n < shot->nt; ++n) {
-        if (ckpt && n % ckpt_every == 0) {
-            char *slot = (char *)ckpt + (size_t)(n / ckpt_every) * ckpt_slot_bytes(L);
-            hipError_t e = hipMemcpyAsync(slot, state->buf[n & 1], L.field, hipMemcpyDeviceToDevice, s);
-            if (e == hipSuccess)
-                e = hipMemcpyAsync(slot + L.field, state->buf[(n + 1) & 1], L.field,
-                                   hipMemcpyDeviceToDevice, s);
-            if (e != hipSuccess) return hip_fail(e, "checkpoint copy");
-        }
-        st = do_step(model, state, shot, n, traces ? traces + (size_t)n * (size_t)nrec : nullptr, s);
-        if (st != FD_OK) return st;
-    }
-    return ok();
+    st = shot_steps(model, state, shot, traces, ckpt, ckpt_every, s);
+    return st == FD_OK ? ok() : st;
 }
 
 struct fd_shot_graph {
@@ -306,9 +527,7 @@ fd_status fd_shot_graph_create(const fd_model *model, fd_state *state, const fd_
         return hip_fail(e, "graph capture start");
     }
     st = do_begin(model, state, shot, cs);
-    const int64_t nrec = nrec_of(shot);
-    for (int64_t n = 0; st == FD_OK && n < shot->nt; ++n)
-        st = do_step(model, state, shot, n, traces ? traces + (size_t)n * (size_t)nrec : nullptr, cs);
+    if (st == FD_OK) st = shot_steps(model, state, shot, traces, nullptr, 0, cs);
     hipGraph_t g = nullptr;
     e = hipStreamEndCapture(cs, &g);  // ends the capture whether or not recording succeeded
     if (st == FD_OK && e == hipSuccess) e = hipGraphInstantiate(&h->exec, g, nullptr, nullptr, 0);
@@ -380,35 +599,8 @@ fd_status fd_run_shots(const fd_model *model, fd_state *const *states, const fd_
         fd_status st = do_begin(model, states[i], shots[i], s);
         if (st != FD_OK) return st;
     }
-    const int64_t nt = shots[0]->nt;
-    for (int64_t n = 0; n < nt; ++n) {
-        for (int32_t i0 = 0; i0 < count; i0 += FD_BATCH_MAX) {
-            fdk::Batch2D b;
-            b.count = 0;
-            for (int32_t i = i0; i < std::min<int32_t>(count, i0 + FD_BATCH_MAX); ++i) {
-                fd_state *st = states[i];
-                if (ckpt && ckpt[i] && n % ckpt_every == 0) {
-                    char *slot = (char *)ckpt[i] + (size_t)(n / ckpt_every) * ckpt_slot_bytes(L);
-                    hipError_t e = hipMemcpyAsync(slot, st->buf[n & 1], L.field, hipMemcpyDeviceToDevice, s);
-                    if (e == hipSuccess)
-                        e = hipMemcpyAsync(slot + L.field, st->buf[(n + 1) & 1], L.field, hipMemcpyDeviceToDevice, s);
-                    if (e != hipSuccess) return hip_fail(e, "checkpoint copy");
-                }
-                StepArgs a = base_args(model, shots[i]);
-                a.cur = st->buf[n & 1];
-                a.prev = st->buf[(n + 1) & 1];
-                a.n = n;
-                const int64_t nrec = nrec_of(shots[i]);
-                a.trace_row = (traces && traces[i] && nrec > 0) ? traces[i] + (size_t)n * (size_t)nrec : nullptr;
-                a.meta = st->meta;
-                b.it[b.count++] = a;
-            }
-            hipError_t e = fdk::launch_step_batch2d(b, fdk::kFwd, s);
-            if (e != hipSuccess) return hip_fail(e, "batched step launch");
-        }
-        for (int32_t i = 0; i < count; ++i) states[i]->next = n + 1;
-    }
-    return ok();
+    const fd_status st = run_steps(model, states, shots, count, traces, ckpt, ckpt_every, s);
+    return st == FD_OK ? ok() : st;
 }
 
 }  // extern "C"
@@ -420,16 +612,142 @@ namespace {
 // history field of every step (L w^n for the gradient, w^n for the image),
 // then the z-form adjoint field is stepped back through the segment
 // accumulating sum_k z^k * hist^{k-1} in FP64, one sum per shot (acc[i],
-// padded, inside work[i]).  In 2D FP32 every step of all shots is one
-// launch of the batched kernel (groups of FD_BATCH_MAX shots); otherwise
-// the shots' steps are launched one by one.  Per shot and cell the
-// arithmetic is the same either way.
+// padded, inside work[i]).  In 2D a launch takes several steps of all shots
+// (groups of FD_BATCH_MAX); in 3D the shots' steps are launched one by one.
+// Per shot and cell the arithmetic is the same either way.
 struct ShotIO {
     const fd_shot *shot;
     const float *adj;
     const void *ckpt;
     void *work;
 };
+
+// The cut of `m` steps into launches for the backward pass: at most `cap`
+// steps each, the larger ones last; `even`: an even number of launches, or
+// one.
+std::vector<int> cut_steps(int64_t m, int cap, bool even)
+{
+    int64_t n = (m + cap - 1) / cap;
+    if (even && n > 1 && (n & 1)) ++n;
+    std::vector<int> out;
+    for (int64_t i = 0; i < n; ++i) out.push_back((int)(m / n + (i >= n - m % n ? 1 : 0)));
+    return out;
+}
+
+// backward_pass on 2D grids: several steps per launch.  Two pairs of levels,
+// the recompute state's and the adjoint state's places in the work buffers,
+// serve the adjoint recursion in turn; while a segment is recomputed, the one
+// that does not hold the adjoint state serves the recompute, which reads the
+// checkpoint where it lies.  The gradient's recompute needs a second pair of
+// its own (the image's does not: its levels go to the history) and takes the
+// segment's last two history fields, which only its last launch writes: that
+// one reads the first pair, since the launches are even in number, and it
+// stores no levels.
+fd_status backward_2d(const fd_model *model, const ShotIO *io, int32_t count, int32_t every, bool image,
+                      hipStream_t s)
+{
+    const Layout &L = model->L;
+    const ptrdiff_t fl = (ptrdiff_t)(L.f32field / 4);
+    auto level = [&](int32_t i, int p, int which) -> float * {   // pair 0: recompute state, 1: adjoint state
+        return (float *)io[i].work + (p == 0 ? which : 2 + every + which) * fl;
+    };
+    auto hist = [&](int32_t i, int64_t slot) -> float * { return (float *)io[i].work + (2 + slot) * fl; };
+    const int64_t nt = io[0].shot->nt, nseg = n_ckpt(nt, every);
+    const int32_t group = std::min<int32_t>(count, FD_BATCH_MAX);
+    std::vector<fdk::MultiGrid> grids((size_t)group, fdk::MultiGrid{(int)L.nz, L.px});
+    const int64_t seg0 = std::min<int64_t>(nt, every);
+    // (at least 2, so that the recompute's last launch writes both fields of
+    // the tail)
+    const int cap = std::max(2, plan_multi(grids.data(), group, seg0, false).steps);
+    auto launch = [&](auto make_args, int mode) -> hipError_t {
+        for (int32_t i0 = 0; i0 < count; i0 += FD_BATCH_MAX) {
+            fdk::MultiArgs it[FD_BATCH_MAX];
+            int k = 0;
+            for (int32_t i = i0; i < std::min<int32_t>(count, i0 + FD_BATCH_MAX); ++i) it[k++] = make_args(i);
+            const hipError_t e = fdk::launch_multi2d(it, k, mode, s);
+            if (e != hipSuccess) return e;
+        }
+        return hipSuccess;
+    };
+    int zp = 1;   // the pair that holds the adjoint state: (z^(k+1), z^(k+2))
+    for (int64_t seg = nseg - 1; seg >= 0; --seg) {
+        const int64_t n0 = seg * every, n1 = std::min<int64_t>(nt, n0 + every), m = n1 - n0;
+        auto saved = [&](int32_t i, int which) -> const float * {
+            return (const float *)((const char *)io[i].ckpt + (size_t)seg * ckpt_slot_bytes(L) + which * L.field);
+        };
+        if (image) {
+            // slot p holds w^(n0+p); slot 0 is the checkpoint's P
+            const std::vector<int> cut = m > 1 ? cut_steps(m - 1, cap, false) : std::vector<int>(1, 0);
+            int64_t p = 0;
+            for (const int k : cut) {
+                const hipError_t e = launch(
+                    [&](int32_t i) {
+                        fdk::MultiArgs a = multi_args(model, io[i].shot, n0 + p, k);
+                        a.cur = p == 0 ? saved(i, 0) : hist(i, p);
+                        a.prev = p == 0 ? saved(i, 1) : hist(i, p - 1);
+                        if (p == 0) a.keep1 = hist(i, 0);
+                        a.hist = k > 0 ? hist(i, p + 1) : nullptr;
+                        a.hist_stride = fl;
+                        return a;
+                    },
+                    fdk::kFwdKeep);
+                if (e != hipSuccess) return hip_fail(e, "recompute steps");
+                p += k;
+            }
+        } else {
+            const std::vector<int> cut = cut_steps(m, cap, true);
+            int64_t p = 0;
+            for (size_t l = 0; l < cut.size(); ++l) {
+                const bool last = l + 1 == cut.size();
+                // launch 0 reads the checkpoint; odd launches read the free
+                // pair, even ones the history's last two fields
+                auto place = [&](int32_t i, size_t after, int which) -> float * {
+                    return (after & 1) == 0 ? level(i, 1 - zp, which) : hist(i, m - 2 + which);
+                };
+                const hipError_t e = launch(
+                    [&](int32_t i) {
+                        fdk::MultiArgs a = multi_args(model, io[i].shot, n0 + p, cut[l]);
+                        a.cur = l == 0 ? saved(i, 0) : place(i, l - 1, 0);
+                        a.prev = l == 0 ? saved(i, 1) : place(i, l - 1, 1);
+                        if (!last) {
+                            a.out1 = place(i, l, 0);
+                            a.out0 = place(i, l, 1);
+                        }
+                        a.hist = hist(i, p);
+                        a.hist_stride = fl;
+                        return a;
+                    },
+                    fdk::kFwdLap);
+                if (e != hipSuccess) return hip_fail(e, "recompute steps");
+                p += cut[l];
+            }
+        }
+        int64_t k = n1;   // adjoint steps k = n1 .. n0+1
+        for (const int c : cut_steps(m, cap, false)) {
+            const hipError_t e = launch(
+                [&](int32_t i) {
+                    fdk::MultiArgs a = multi_args(model, io[i].shot, 0, c);
+                    const int64_t nrec = nrec_of(io[i].shot);
+                    a.nt = 0;  // no source in the adjoint recursion
+                    a.cur = level(i, zp, 0);
+                    a.prev = level(i, zp, 1);
+                    a.out1 = level(i, 1 - zp, 0);
+                    a.out0 = level(i, 1 - zp, 1);
+                    a.resid = nrec > 0 ? io[i].adj + (size_t)(k - 1) * (size_t)nrec : nullptr;
+                    a.rec_stride = -nrec;
+                    a.hist = hist(i, k - 1 - n0);
+                    a.hist_stride = -fl;
+                    a.g = (double *)((float *)io[i].work + (4 + every) * fl);
+                    return a;
+                },
+                fdk::kAdj);
+            if (e != hipSuccess) return hip_fail(e, "adjoint steps");
+            zp = 1 - zp;
+            k -= c;
+        }
+    }
+    return FD_OK;
+}
 
 fd_status backward_pass(const fd_model *model, const ShotIO *io, int32_t count, size_t ckpt_bytes,
                         int32_t ckpt_every, size_t work_bytes, bool image, hipStream_t s,
@@ -466,21 +784,9 @@ fd_status backward_pass(const fd_model *model, const ShotIO *io, int32_t count, 
     auto gsum = [&](int32_t i) -> double * {
         return (double *)((char *)io[i].work + (4 + (size_t)ckpt_every) * L.f32field);
     };
-    const bool batched = L.ndim == 2 && count > 1;
-    // one step of every shot: batched launches in 2D, one launch per shot otherwise
     auto launch_all = [&](auto make_args, int mode) -> hipError_t {
-        if (!batched) {
-            for (int32_t i = 0; i < count; ++i) {
-                hipError_t e = fdk::launch_step(make_args(i), L.ndim, L.storage, mode, s);
-                if (e != hipSuccess) return e;
-            }
-            return hipSuccess;
-        }
-        for (int32_t i0 = 0; i0 < count; i0 += FD_BATCH_MAX) {
-            fdk::Batch2D b;
-            b.count = 0;
-            for (int32_t i = i0; i < std::min<int32_t>(count, i0 + FD_BATCH_MAX); ++i) b.it[b.count++] = make_args(i);
-            hipError_t e = fdk::launch_step_batch2d(b, mode, s);
+        for (int32_t i = 0; i < count; ++i) {
+            hipError_t e = fdk::launch_step(make_args(i), L.ndim, L.storage, mode, s);
             if (e != hipSuccess) return e;
         }
         return hipSuccess;
@@ -489,7 +795,9 @@ fd_status backward_pass(const fd_model *model, const ShotIO *io, int32_t count, 
     for (int32_t i = 0; i < count; ++i) {
         hipError_t e = fdk::launch_fill_u32(zf(i, 0), (2 * L.f32field + align_up(L.npad * 8)) / 4, 0u, s);
         if (e != hipSuccess) return hip_fail(e, "adjoint clear");
+        acc[i] = gsum(i);
     }
+    if (L.ndim == 2) return backward_2d(model, io, count, ckpt_every, image, s);
     auto ckpt_slot = [&](int32_t i, int64_t seg) -> char * {
         return (char *)io[i].ckpt + (size_t)seg * ckpt_slot_bytes(L);
     };
@@ -573,7 +881,6 @@ fd_status backward_pass(const fd_model *model, const ShotIO *io, int32_t count, 
             if (e != hipSuccess) return hip_fail(e, "adjoint step");
         }
     }
-    for (int32_t i = 0; i < count; ++i) acc[i] = gsum(i);
     return FD_OK;
 }
 
@@ -669,7 +976,7 @@ fd_status fd_set_wavefield(fd_state *state, int32_t which, const float *in, void
     const Layout &L = state->m->L;
     hipStream_t s = (hipStream_t)stream;
     if (state->next < 0) {
-        hipError_t e = fdk::launch_fill_u32(state->base, L.state_bytes / 4, 0u, s);
+        hipError_t e = fdk::launch_fill_u32(state->base, L.state_least / 4, 0u, s);
         if (e != hipSuccess) return hip_fail(e, "fd_set_wavefield clear");
         state->next = 0;
     }
@@ -823,35 +1130,13 @@ fd_status fd_step_batch(fd_batch_item *items, int32_t count, int32_t nsteps, voi
         for (int32_t j = 0; j < i; ++j)
             if (items[j].state == it.state) return fail(FD_ERR_INVALID_ARG, "item %d repeats a state", i);
     }
-    hipStream_t s = (hipStream_t)stream;
-    for (int32_t step = 0; step < nsteps; ++step) {
-        fdk::Batch2D b;
-        b.count = 0;
-        int32_t which[FD_BATCH_MAX];
-        for (int32_t i = 0; i < count; ++i) {
-            fd_batch_item &it = items[i];
-            if (it.n >= it.shot->nt) continue;
-            StepArgs a = base_args(it.model, it.shot);
-            a.cur = it.state->buf[it.n & 1];
-            a.prev = it.state->buf[(it.n + 1) & 1];
-            a.n = it.n;
-            a.trace_row = (it.traces && nrec_of(it.shot) > 0)
-                              ? it.traces + (size_t)it.n * (size_t)nrec_of(it.shot) : nullptr;
-            a.meta = it.state->meta;
-            b.it[b.count] = a;
-            which[b.count] = i;
-            ++b.count;
-        }
-        if (b.count == 0) break;
-        hipError_t e = fdk::launch_step_batch2d(b, fdk::kFwd, s);
-        if (e != hipSuccess) return hip_fail(e, "batched step launch");
-        for (int32_t k = 0; k < b.count; ++k) {
-            fd_batch_item &it = items[which[k]];
-            it.n += 1;
-            it.state->next = it.n;
-        }
-    }
-    return ok();
+    Flight f[FD_BATCH_MAX];
+    for (int32_t i = 0; i < count; ++i)
+        f[i] = Flight{items[i].model, items[i].state, items[i].shot, items[i].n,
+                      std::min<int64_t>(items[i].shot->nt, items[i].n + nsteps), items[i].traces, nullptr};
+    const fd_status st = advance(f, count, (hipStream_t)stream);
+    for (int32_t i = 0; i < count; ++i) items[i].n = f[i].n;   // what has been enqueued
+    return st == FD_OK ? ok() : st;
 }
 
 }  // extern "C"

@@ -11,7 +11,8 @@ namespace fdk {
 enum Mode : int {
     kFwd = 0,     // forward step
     kFwdLap = 1,  // forward step that also stores L(cur) (gradient recompute)
-    kAdj = 2      // adjoint step: receiver injection of c G r, g += new * hist
+    kAdj = 2,     // adjoint step: receiver injection of c G r, g += new * hist
+    kFwdKeep = 3  // forward steps of one launch that also store every new level
 };
 
 // Forward modes that write a per-step history field (StepArgs::lap).
@@ -63,6 +64,30 @@ struct StepArgs {
     const float *lap3;    // kAdj, gmode 3: history of level k+1
     const float *resid_row;  // kAdj: dJ/dtraces row k-1 (nrec), or null
     double *g;            // kAdj: FP64 accumulator, padded
+};
+
+// Arguments of S consecutive 2D FP32 steps on one grid in one launch.  Steps
+// s = 0 .. S-1 are the time steps n + s (forward) or n - s (adjoint); rows of
+// traces or residuals and history fields move by their stride each step.
+struct MultiArgs {
+    const float *cur, *prev;  // the two levels at hand, read only
+    float *out1, *out0;       // the last level and the one before it, or null
+    float *keep1, *keep0;     // copies of cur and prev (a checkpoint), or null
+    const float *c, *gz, *gx;
+    const float *wavelet;
+    float *trace;             // trace row of step 0, or null
+    const float *resid;       // kAdj: dJ/dtraces row of step 0, or null
+    float *hist;              // kFwdLap, kFwdKeep: out; kAdj: in (step 0's field)
+    double *g;                // kAdj: FP64 accumulator
+    int64_t rec_stride;       // floats from one step's row to the next
+    int64_t hist_stride;      // floats from one step's history field to the next
+    int64_t n, nt;
+    int32_t nz, nx, px;
+    int32_t sz, sx;
+    float amp;
+    int32_t rz0, rx0, rnz, rnx, rdz, rdx;  // the receiver box
+    int32_t steps;            // S (0: the levels only pass through)
+    int32_t tiles_x;          // set by the launcher
 };
 
 // Layout of the 16-bit storage bookkeeping ("meta", in the state buffer):

@@ -61,7 +61,9 @@ Layout make_layout(const fd_grid &g)
     L.scratch_off = L.gx_off + align_up((size_t)g.nx * 4);
     L.model_bytes = L.scratch_off + kAlign;
     L.meta_off = 2 * L.field;
-    L.state_bytes = L.meta_off + align_up(fdk::kMetaWords * 4);
+    L.state_least = L.meta_off + align_up(fdk::kMetaWords * 4);
+    L.pair_off = g.ndim == 2 && g.storage == FD_F32 ? L.state_least : 0;
+    L.state_bytes = L.state_least + (L.pair_off ? 2 * L.field : 0);
     return L;
 }
 

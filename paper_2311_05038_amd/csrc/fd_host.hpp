@@ -39,7 +39,11 @@ struct Layout {
     size_t f32field;   // bytes of one FP32 padded field, aligned
     size_t cfield;     // bytes of the stored c (FP32 or 16-bit fixed point), aligned
     size_t c_off, gz_off, gy_off, gx_off, scratch_off, model_bytes;
-    size_t state_bytes, meta_off;
+    // state buffer: two levels, the bookkeeping, and on 2D FP32 grids a second
+    // pair of levels at pair_off (0: none) that launches of several steps
+    // write in turn; state_least is the size without it, which is enough for
+    // every call (each step is then a launch of its own)
+    size_t state_bytes, meta_off, state_least, pair_off;
     // z-slab of a larger grid: global index of plane 0, global plane count
     // (nz for an ordinary grid), and the bytes of the 4 ghost planes that
     // precede (and follow) a slab's stored level (0 for an ordinary grid)
@@ -89,6 +93,7 @@ struct fd_state {
     const fd_model *m;
     void *base;    // the state buffer
     void *buf[2];  // plane 0 of each stored level (past a slab's leading ghosts)
+    float *pair[2];  // the second pair of levels, or null (see Layout)
     int32_t *meta;
     int64_t next;  // next step index, -1 before fd_begin_shot
 };

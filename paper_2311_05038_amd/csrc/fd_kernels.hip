@@ -182,12 +182,13 @@ __device__ __forceinline__ float update(float G, float ctr, float c, float lap, 
 // 2D
 // --------------------------------------------------------------------------
 // CQ: c is read as 16-bit fixed-point codes (16-bit fields, forward step).
-template <int ST, int VX, int MODE, bool CQ>
+template <int ST, int VX, bool CQ>
 __device__ __forceinline__ void step2d_tile(const StepArgs &a, int tx, int tz,
                                             float (*row)[64 * VX + 8], const HalfCtx &h,
                                             float inj, float &bmax)
 {
-    static_assert(!CQ || (ST != kF32 && MODE == kFwd), "16-bit c: 16-bit fields, forward step");
+    static_assert(!CQ || ST != kF32, "16-bit c: 16-bit fields");
+    constexpr int MODE = kFwd;
     using T = typename Stor<ST>::T;
     using CT = std::conditional_t<CQ, uint16_t, float>;
     constexpr int TX = 64 * VX;
@@ -312,7 +313,7 @@ __device__ __forceinline__ void step2d_tile(const StepArgs &a, int tx, int tz,
             }
             G[v] = gzz * gxv[v];
             nw[v] = update<ST>(G[v], q[4][v], cc[v], lap, pc[v], h);
-            lp[v] = MODE == kAdj ? q[4][v] : lap;
+            lp[v] = lap;
         }
         finish_cells<ST, VX, MODE, false, false>(a, h, z, 0, x0, lane_in, (size_t)z * px, (uint32_t)x0, nw,
                                                  lp, pc, cc, G, inj, bmax, out);
@@ -325,7 +326,7 @@ __device__ __forceinline__ void step2d_tile(const StepArgs &a, int tx, int tz,
     flush<T, VX, MODE, false>(out);
 }
 
-template <int ST, int VX, int MODE, bool CQ>
+template <int ST, int VX, bool CQ>
 __global__ __launch_bounds__(64) void k_step2d(StepArgs a)
 {
     __shared__ float row[2][64 * VX + 8];
@@ -333,18 +334,17 @@ __global__ __launch_bounds__(64) void k_step2d(StepArgs a)
     const int t = xcd_tile(blockIdx.x, nb);
     const int tx = t % a.tiles_x, tz = t / a.tiles_x;
     float inj = 0.0f;
-    if constexpr (MODE != kAdj)
-        if (a.n + 1 < a.nt) inj = a.amp * a.wavelet[a.n + 1];
+    if (a.n + 1 < a.nt) inj = a.amp * a.wavelet[a.n + 1];
     const HalfCtx h = half_prologue<ST>(a, inj, blockIdx.x == 0);
     float bmax = 0.0f;
-    step2d_tile<ST, VX, MODE, CQ>(a, tx, tz, row, h, inj, bmax);
+    step2d_tile<ST, VX, CQ>(a, tx, tz, row, h, inj, bmax);
     if constexpr (ST != kF32)
         block_max_to<64>(max_slot(a.meta, (int)((a.n + 1) & 3)), bmax * h.sn, nullptr);
 }
 
-// Batched 2D FP32 step (any mode): block b belongs to the item whose tile
-// range holds b; every item keeps its own grid, fields and step index.
-template <int VX, int MODE>
+// Batched 2D FP32 step: block b belongs to the item whose tile range holds
+// b; every item keeps its own grid, fields and step index.
+template <int VX>
 __global__ __launch_bounds__(64) void k_step2d_batch(Batch2D b)
 {
     __shared__ float row[2][64 * VX + 8];
@@ -355,11 +355,10 @@ __global__ __launch_bounds__(64) void k_step2d_batch(Batch2D b)
     const int lt = t - b.begin[i];
     const int tx = lt % a.tiles_x, tz = lt / a.tiles_x;
     float inj = 0.0f;
-    if constexpr (MODE != kAdj)
-        if (a.n + 1 < a.nt) inj = a.amp * a.wavelet[a.n + 1];
+    if (a.n + 1 < a.nt) inj = a.amp * a.wavelet[a.n + 1];
     const HalfCtx h{1.0f, 1.0f, 1.0f, 1.0f};
     float bmax = 0.0f;
-    step2d_tile<kF32, VX, MODE, false>(a, tx, tz, row, h, inj, bmax);
+    step2d_tile<kF32, VX, false>(a, tx, tz, row, h, inj, bmax);
 }
 
 // --------------------------------------------------------------------------
@@ -1137,20 +1136,18 @@ static void launch3d(const StepArgs &a, int nb, hipStream_t s)
 }
 
 template <int VX>
-static void launch2d(const StepArgs &a, int storage, int mode, int nb, hipStream_t s)
+static void launch2d(const StepArgs &a, int storage, int nb, hipStream_t s)
 {
     const dim3 g(nb), b(64);
     const bool cq = a.c16 != nullptr;
     if (storage == kF32) {
-        if (mode == kFwd) hipLaunchKernelGGL((k_step2d<kF32, VX, kFwd, false>), g, b, 0, s, a);
-        else if (mode == kFwdLap) hipLaunchKernelGGL((k_step2d<kF32, VX, kFwdLap, false>), g, b, 0, s, a);
-        else hipLaunchKernelGGL((k_step2d<kF32, VX, kAdj, false>), g, b, 0, s, a);
+        hipLaunchKernelGGL((k_step2d<kF32, VX, false>), g, b, 0, s, a);
     } else if (storage == kF16) {
-        if (cq) hipLaunchKernelGGL((k_step2d<kF16, VX, kFwd, true>), g, b, 0, s, a);
-        else hipLaunchKernelGGL((k_step2d<kF16, VX, kFwd, false>), g, b, 0, s, a);
+        if (cq) hipLaunchKernelGGL((k_step2d<kF16, VX, true>), g, b, 0, s, a);
+        else hipLaunchKernelGGL((k_step2d<kF16, VX, false>), g, b, 0, s, a);
     } else {
-        if (cq) hipLaunchKernelGGL((k_step2d<kBF16, VX, kFwd, true>), g, b, 0, s, a);
-        else hipLaunchKernelGGL((k_step2d<kBF16, VX, kFwd, false>), g, b, 0, s, a);
+        if (cq) hipLaunchKernelGGL((k_step2d<kBF16, VX, true>), g, b, 0, s, a);
+        else hipLaunchKernelGGL((k_step2d<kBF16, VX, false>), g, b, 0, s, a);
     }
 }
 
@@ -1158,11 +1155,13 @@ hipError_t launch_step(StepArgs a, int ndim, int storage, int mode, hipStream_t 
 {
     // 16-bit c is built for the forward step on 16-bit fields only
     if (a.c16 != nullptr && (storage == kF32 || mode != kFwd)) return hipErrorInvalidValue;
+    // the history and adjoint modes in 2D are launch_multi2d's
+    if (ndim == 2 && mode != kFwd) return hipErrorInvalidValue;
     plan_tiles(a, ndim, storage, false);
     const int nb = a.tiles_x * a.tiles_y * a.tiles_z;
     if (ndim == 2) {
-        if (a.vx == 2) launch2d<2>(a, storage, mode, nb, s);
-        else launch2d<1>(a, storage, mode, nb, s);
+        if (a.vx == 2) launch2d<2>(a, storage, nb, s);
+        else launch2d<1>(a, storage, nb, s);
     } else {
         if (storage == kF32) {
             if (mode == kFwd) launch3d<kF32, kFwd>(a, nb, s);
@@ -1179,7 +1178,7 @@ hipError_t launch_step(StepArgs a, int ndim, int storage, int mode, hipStream_t 
     return hipGetLastError();
 }
 
-hipError_t launch_step_batch2d(Batch2D &b, int mode, hipStream_t s)
+hipError_t launch_step_batch2d(Batch2D &b, hipStream_t s)
 {
     int total = 0;
     for (int i = 0; i < b.count; ++i) {
@@ -1189,11 +1188,7 @@ hipError_t launch_step_batch2d(Batch2D &b, int mode, hipStream_t s)
     }
     b.begin[b.count] = total;
     if (total == 0) return hipSuccess;
-    switch (mode) {
-    case kFwd: hipLaunchKernelGGL((k_step2d_batch<kBatchVX, kFwd>), dim3(total), dim3(64), 0, s, b); break;
-    case kFwdLap: hipLaunchKernelGGL((k_step2d_batch<kBatchVX, kFwdLap>), dim3(total), dim3(64), 0, s, b); break;
-    default: hipLaunchKernelGGL((k_step2d_batch<kBatchVX, kAdj>), dim3(total), dim3(64), 0, s, b); break;
-    }
+    hipLaunchKernelGGL(k_step2d_batch<kBatchVX>, dim3(total), dim3(64), 0, s, b);
     return hipGetLastError();
 }
 

@@ -22,8 +22,29 @@ static_assert(sizeof(Batch2D) <= 4096, "batched step arguments must fit the kern
 // (batched: the tile width of the batched 2D kernel).
 void plan_tiles(StepArgs &a, int ndim, int storage, bool batched);
 
+// The same for launches of several 2D FP32 steps (one item: a lone shot).
+template <int N>
+struct MultiBatch {
+    int32_t total;         // tiles of all items
+    int32_t count;
+    int32_t begin[N + 1];  // the items' first tiles
+    MultiArgs it[N];
+};
+static_assert(sizeof(MultiBatch<kBatchMax>) <= 4096, "batched multi-step arguments must fit the kernel-argument segment");
+
 hipError_t launch_step(StepArgs a, int ndim, int storage, int mode, hipStream_t s);
-hipError_t launch_step_batch2d(Batch2D &b, int mode, hipStream_t s);
+hipError_t launch_step_batch2d(Batch2D &b, hipStream_t s);
+// Several steps of up to kBatchMax 2D FP32 grids in one launch (modes kFwd,
+// kFwdLap, kFwdKeep, kAdj); every item takes its own number of steps, at most
+// kMultiSteps.
+constexpr int kMultiSteps = 12;
+hipError_t launch_multi2d(const MultiArgs *items, int count, int mode, hipStream_t s);
+// The tile shape that launch_multi2d takes for `steps` steps on these grids
+// (rows, row pitch), -1 if there is none, and the launch's modelled time.
+struct MultiGrid {
+    int nz, px;
+};
+int multi2d_shape(const MultiGrid *grids, int count, int steps, double *us);
 // The step as separate routine kernels (derivative fields dzz, dxx and, in
 // 3D, dyy materialised in HBM); FP32 fields only.
 hipError_t launch_routines(const StepArgs &a, int ndim, float *dzz, float *dxx, float *dyy,
