@@ -212,12 +212,18 @@ struct HalfCtx {
     float sn_inv;   // 2^-en: value -> storage units (source term)
 };
 
-__device__ __forceinline__ float level_max(const int32_t *meta, int level)
+// The larger magnitude of two levels (or of one, given twice), the same in
+// every lane: each lane reads one slot of each level and the wave takes the
+// maximum.  (Read one after another by every lane, the 128 words cost each
+// block several memory latencies before its first load: BF16 1201 x 1747, 12.4
+// us a step.)
+__device__ __forceinline__ float level_max(const int32_t *meta, int la, int lb)
 {
-    uint32_t m = 0;
-#pragma unroll 16
-    for (int k = 0; k < kMaxSlots; ++k) m = max(m, (uint32_t)meta[kMaxBase + level * kMaxSlots + k]);
-    return __uint_as_float(m);
+    static_assert(kMaxSlots == 64, "one slot per lane");
+    const int lane = threadIdx.x & 63;
+    uint32_t m = max((uint32_t)meta[kMaxBase + la * kMaxSlots + lane], (uint32_t)meta[kMaxBase + lb * kMaxSlots + lane]);
+    for (int off = 32; off >= 1; off >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, off, 64));
+    return __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)m));
 }
 
 template <int ST>
@@ -228,8 +234,7 @@ __device__ __forceinline__ HalfCtx half_prologue(const StepArgs &a, float inj, b
         const int ic = (int)(a.n & 3), ip = (int)((a.n + 3) & 3);
         const int in = (int)((a.n + 1) & 3), iz = (int)((a.n + 2) & 3);
         const int ec = a.meta[ic], ep = a.meta[ip];
-        float m = fmaxf(level_max(a.meta, ic), level_max(a.meta, ip));
-        m = fmaxf(m, fabsf(inj));
+        const float m = fmaxf(level_max(a.meta, ic, ip), fabsf(inj));
         const int en = storage_exponent(m);
         // ec - en and ep - en stay within a few units (the magnitude changes
         // by a bounded factor per step); the clamp only keeps 2^k finite.

@@ -667,6 +667,20 @@ __global__ void k_fill_u32(uint32_t *p, size_t n, uint32_t val)
     for (; i < n; i += stride) p[i] = val;
 }
 
+// f(i, row, x) for every element i = row n + x of nrows rows of n.  A grid
+// holds fewer than 2^32 - 2^23 elements, so the division that finds the row is
+// a 32-bit one (a 64-bit one per element cost these kernels as much as their
+// memory traffic: k_get_field at 512^3 252 us for 1.07 GB).
+template <typename F>
+__device__ __forceinline__ void for_elements(int64_t nrows, int32_t n, F f)
+{
+    const uint32_t total = (uint32_t)nrows * (uint32_t)n, stride = gridDim.x * blockDim.x;
+    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < total; i += stride) {
+        const uint32_t row = i / (uint32_t)n;
+        f((size_t)i, (size_t)row, (size_t)(i - row * (uint32_t)n));
+    }
+}
+
 // c = (v dt/h)^2 rounded from FP64 to FP32.
 __device__ __forceinline__ float model_c(float v, double r)
 {
@@ -675,27 +689,35 @@ __device__ __forceinline__ float model_c(float v, double r)
 }
 
 // c padded (skipped when c is null); also the velocity range (max as float
-// bits) and a flag for non-positive or non-finite values.
-__global__ void k_model_c(const float *__restrict__ v, float *__restrict__ c, int64_t nrows,
-                          int32_t nx, int32_t px, double r, uint32_t *scratch)
+// bits) and a flag for non-positive or non-finite values.  A block folds its
+// maximum in once, and only if it exceeds what is there: with one atomic per
+// wave the kernel was bound by those on one word (1024^2 190 us, 512^3 514).
+__global__ __launch_bounds__(256) void k_model_c(const float *__restrict__ v, float *__restrict__ c, int64_t nrows,
+                                                 int32_t nx, int32_t px, double r, uint32_t *scratch)
 {
+    __shared__ uint32_t red[2][4];
     uint32_t vmax = 0, bad = 0;
-    const size_t total = (size_t)nrows * nx;
-    size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const size_t stride = (size_t)gridDim.x * blockDim.x;
-    for (; i < total; i += stride) {
-        const size_t rw = i / (size_t)nx, x = i - rw * (size_t)nx;
+    for_elements(nrows, nx, [&](size_t i, size_t rw, size_t x) {
         const float vi = v[i];
         if (!(vi > 0.0f) || !(vi < 3.0e38f)) bad = 1;
         vmax = max(vmax, __float_as_uint(fabsf(vi)));
         if (c != nullptr) c[rw * (size_t)px + x] = model_c(vi, r);
-    }
+    });
     for (int off = 32; off >= 1; off >>= 1) {
         vmax = max(vmax, (uint32_t)__shfl_xor((int)vmax, off, 64));
         bad |= (uint32_t)__shfl_xor((int)bad, off, 64);
     }
     if ((threadIdx.x & 63) == 0) {
-        atomicMax(&scratch[0], vmax);
+        red[0][threadIdx.x >> 6] = vmax;
+        red[1][threadIdx.x >> 6] = bad;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int k = 1; k < 4; ++k) {
+            vmax = max(vmax, red[0][k]);
+            bad |= red[1][k];
+        }
+        if (vmax > __atomic_load_n(&scratch[0], __ATOMIC_RELAXED)) atomicMax(&scratch[0], vmax);
         if (bad) atomicOr(&scratch[1], 1u);
     }
 }
@@ -705,14 +727,10 @@ __global__ void k_model_c(const float *__restrict__ v, float *__restrict__ c, in
 __global__ void k_model_c16(const float *__restrict__ v, uint16_t *__restrict__ c16, int64_t nrows,
                             int32_t nx, int32_t px, double r, float inv_scale)
 {
-    const size_t total = (size_t)nrows * nx;
-    size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const size_t stride = (size_t)gridDim.x * blockDim.x;
-    for (; i < total; i += stride) {
-        const size_t rw = i / (size_t)nx, x = i - rw * (size_t)nx;
+    for_elements(nrows, nx, [&](size_t i, size_t rw, size_t x) {
         const float q = fminf(rintf(model_c(v[i], r) * inv_scale), 65535.0f);
         c16[rw * (size_t)px + x] = (uint16_t)q;
-    }
+    });
 }
 
 // First source addition of a shot into the zeroed level-0 field (+ the
@@ -747,13 +765,9 @@ __global__ void k_get_field(const void *buf, float *__restrict__ out, int64_t nr
     using T = typename Stor<ST>::T;
     float s = 1.0f;
     if constexpr (ST != kF32) s = pow2i(meta[level_slot]);
-    const size_t total = (size_t)nrows * nx;
-    size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const size_t stride = (size_t)gridDim.x * blockDim.x;
-    for (; i < total; i += stride) {
-        const size_t rw = i / (size_t)nx, x = i - rw * (size_t)nx;
+    for_elements(nrows, nx, [&](size_t i, size_t rw, size_t x) {
         out[i] = decode<ST>(((const T *)buf)[rw * (size_t)px + x], s);
-    }
+    });
 }
 
 // max |x| over a dense array, folded into slots[blockIdx % kMaxSlots] as
@@ -778,20 +792,16 @@ __global__ void k_set_field(const float *__restrict__ in, void *buf, int64_t nro
     using T = typename Stor<ST>::T;
     float inv = 1.0f;
     if constexpr (ST != kF32) {
-        const int e = storage_exponent(level_max(meta, slot));
+        const int e = storage_exponent(level_max(meta, slot, slot));
         inv = pow2i(-e);
         if (blockIdx.x == 0 && threadIdx.x == 0) meta[slot] = e;
     }
-    const size_t total = (size_t)nrows * px;
-    size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const size_t stride = (size_t)gridDim.x * blockDim.x;
     bool bad = false;
-    for (; i < total; i += stride) {
-        const size_t rw = i / (size_t)px, x = i - rw * (size_t)px;
+    for_elements(nrows, px, [&](size_t i, size_t rw, size_t x) {
         const float v = x < (size_t)nx ? in[rw * (size_t)nx + x] : 0.0f;
         bad |= !(fabsf(v) <= 3.4028235e38f);
         ((T *)buf)[i] = encode<ST>(v, inv);
-    }
+    });
     // a non-finite value set into the shot is recorded in its health flags
     if (__ballot(bad) != 0 && (threadIdx.x & 63) == 0) atomicOr((uint32_t *)&meta[kHealth], kNonfiniteInput);
 }
@@ -832,27 +842,17 @@ __global__ void k_grad_finish(const double *__restrict__ g, const float *__restr
                               double *__restrict__ grad_v, int64_t nrows, int32_t nx, int32_t px,
                               double two_dt_over_h)
 {
-    const size_t total = (size_t)nrows * nx;
-    size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const size_t stride = (size_t)gridDim.x * blockDim.x;
-    for (; i < total; i += stride) {
-        const size_t rw = i / (size_t)nx, x = i - rw * (size_t)nx;
+    for_elements(nrows, nx, [&](size_t i, size_t rw, size_t x) {
         const size_t p = rw * (size_t)px + x;
         grad_v[i] += g[p] * two_dt_over_h / sqrt((double)c[p]);
-    }
+    });
 }
 
 // image += the accumulated zero-lag correlation (padded -> dense).
 __global__ void k_image_finish(const double *__restrict__ g, double *__restrict__ image,
                                int64_t nrows, int32_t nx, int32_t px)
 {
-    const size_t total = (size_t)nrows * nx;
-    size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const size_t stride = (size_t)gridDim.x * blockDim.x;
-    for (; i < total; i += stride) {
-        const size_t rw = i / (size_t)nx, x = i - rw * (size_t)nx;
-        image[i] += g[rw * (size_t)px + x];
-    }
+    for_elements(nrows, nx, [&](size_t i, size_t rw, size_t x) { image[i] += g[rw * (size_t)px + x]; });
 }
 
 // --------------------------------------------------------------------------
@@ -877,7 +877,7 @@ hipError_t launch_fill_u32(void *p, size_t nwords, uint32_t val, hipStream_t s)
 hipError_t launch_model_c(const float *v, float *c, int64_t nrows, int32_t nx, int32_t px,
                           double r, uint32_t *scratch, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_model_c, dim3(grid_blocks((size_t)nrows * nx, 256)), dim3(256), 0, s,
+    hipLaunchKernelGGL(k_model_c, dim3(std::min(2048, (grid_blocks((size_t)nrows * nx, 256) + 3) / 4)), dim3(256), 0, s,
                        v, c, nrows, nx, px, r, scratch);
     return hipGetLastError();
 }

@@ -69,17 +69,6 @@ __device__ __forceinline__ void load_to_lds16(const float *g, float *lds)
                                      (__attribute__((address_space(3))) void *)lds, 16, 0, 0);
 }
 
-// The item whose tiles hold t.  A lone item needs no look-up: its arguments
-// are then at fixed places, and their loads do not wait for one another.
-template <int N>
-__device__ __forceinline__ int item_of(const MultiBatch<N> &b, int t)
-{
-    int i = 0;
-    if constexpr (N > 1)
-        while (i + 1 < b.count && t >= b.begin[i + 1]) ++i;
-    return i;
-}
-
 template <int TXL, int RZ, int NZ, int MODE, int WPS, int N>
 __global__ __launch_bounds__(TXL *NZ, WPS) void k_multi2d(const MultiBatch<N> b)
 {
@@ -96,9 +85,21 @@ __global__ __launch_bounds__(TXL *NZ, WPS) void k_multi2d(const MultiBatch<N> b)
     const int per = (total + 7) >> 3, xcd = blockIdx.x & 7, stride = (int)(gridDim.x >> 3);
     const int tend = min(total, (xcd + 1) * per);
 
+    // The item whose tiles hold t: lane i holds item i's first tile.  (A walk
+    // over them by scalar loads, each waiting for the one before, cost 1 us a
+    // tile.)  A lone item's arguments are at fixed places instead.
+    int first_tile = INT32_MAX;
+    if constexpr (N > 1)
+        if ((int)(threadIdx.x & 63) < b.count) first_tile = b.begin[threadIdx.x & 63];
+    auto item_of = [&](int t) -> int {
+        if constexpr (N > 1)
+            return __popcll(__ballot(first_tile <= t)) - 1;
+        else
+            return 0;
+    };
+
     // P of tile t into `buf` (rows and columns clamped into the field)
-    auto fetch = [&](int t, float *buf) {
-        const int i = item_of(b, t);
+    auto fetch = [&](int t, int i, float *buf) {
         const MultiArgs &a = b.it[i];
         const int lt = t - b.begin[i], tz = lt / a.tiles_x, tx = lt - tz * a.tiles_x;
         const int zb = tz * (EZ - 8 * a.steps) - 4 * a.steps, xb = tx * (EX - 8 * a.steps) - 4 * a.steps;
@@ -114,9 +115,9 @@ __global__ __launch_bounds__(TXL *NZ, WPS) void k_multi2d(const MultiBatch<N> b)
 
     int t = xcd * per + (int)(blockIdx.x >> 3);
     if (t >= tend) return;
-    fetch(t, buf0);
+    int it = item_of(t);
+    fetch(t, it, buf0);
     for (bool first = true;; first = false) {
-        const int it = item_of(b, t);
         const MultiArgs &a = b.it[it];
         const int S = a.steps, H = 4 * S;
         const int lt = t - b.begin[it], tz = lt / a.tiles_x, tx = lt - tz * a.tiles_x;
@@ -189,7 +190,7 @@ __global__ __launch_bounds__(TXL *NZ, WPS) void k_multi2d(const MultiBatch<N> b)
             put(buf0, A);
         }
         // whole rows of the tile's inner region (clipped to the field) to dst
-        auto store = [&](float *dst, const float (&u)[RZ][4]) {
+        auto store = [&](float *dst, const float (&u)[RZ][4], bool stream = false) {
             if (dst != nullptr && own_x) {
                 int zo = z0, xo = x0;
                 asm volatile("" : "+v"(zo), "+v"(xo));   // keep no derived address in registers
@@ -200,7 +201,10 @@ __global__ __launch_bounds__(TXL *NZ, WPS) void k_multi2d(const MultiBatch<N> b)
                         Pack<float, 4> p;
 #pragma unroll
                         for (int v = 0; v < 4; ++v) p.v[v] = u[r][v];
-                        stp<float, 4>(dst + (size_t)z * a.px + xo, p);
+                        if (stream)
+                            stp_stream<float, 4>(dst + (size_t)z * a.px + xo, p);
+                        else
+                            stp<float, 4>(dst + (size_t)z * a.px + xo, p);
                     }
                 }
             }
@@ -310,14 +314,16 @@ __global__ __launch_bounds__(TXL *NZ, WPS) void k_multi2d(const MultiBatch<N> b)
             if (s + 1 < S) put(dst, o);
             if constexpr (MODE == kFwdLap) {
                 if (edge) mask(lzz);
-                store(a.hist + s * a.hist_stride, lzz);
+                store(a.hist + s * a.hist_stride, lzz, true);
             }
             if constexpr (MODE == kFwdKeep) store(a.hist + s * a.hist_stride, o);
             if constexpr (MODE == kAdj) {
-                // the gradient's FP64 sum, one pass for two steps (or the last
-                // one alone), each cell's terms in the order of the steps
-                const bool two = pair;
-                if ((two || s + 1 == S) && own_x) {
+                // the gradient's FP64 sum: one pass over it for two steps (or
+                // the last one alone), each cell's terms in the order of the
+                // steps.  (Held in registers for all S steps, which 3 rows a
+                // thread leave room for, it measured slower: 37 us a step
+                // for 8 x 1024^2 against 33.)
+                if ((pair || s + 1 == S) && own_x) {
 #pragma unroll
                     for (int r = 0; r < RZ; ++r) {
                         const int row = zo - zb + r, z = zo + r;
@@ -325,9 +331,9 @@ __global__ __launch_bounds__(TXL *NZ, WPS) void k_multi2d(const MultiBatch<N> b)
                             const size_t e = (size_t)z * a.px + xo;
                             const float *h = a.hist + s * a.hist_stride + e;
                             Pack<double, 4> g = ldp<double, 4>(a.g + e);
-                            const Pack<float, 4> h1 = ldp<float, 4>(h);
-                            if (two) {
-                                const Pack<float, 4> h2 = ldp<float, 4>(h - a.hist_stride);
+                            const Pack<float, 4> h1 = ldp_stream<float, 4>(h);
+                            if (pair) {
+                                const Pack<float, 4> h2 = ldp_stream<float, 4>(h - a.hist_stride);
 #pragma unroll
                                 for (int v = 0; v < 4; ++v) g.v[v] = fma((double)u[r][v], (double)h2.v[v], g.v[v]);
                             }
@@ -340,7 +346,7 @@ __global__ __launch_bounds__(TXL *NZ, WPS) void k_multi2d(const MultiBatch<N> b)
             }
         };
 
-        const int tn = t + stride;
+        const int tn = t + stride, in = tn < tend ? item_of(tn) : 0;
         int s = 0;
         for (; s + 2 < S; s += 2) {
             step(s, buf0, buf1, A, B, false);
@@ -351,7 +357,7 @@ __global__ __launch_bounds__(TXL *NZ, WPS) void k_multi2d(const MultiBatch<N> b)
             // the last step reads buf1 and writes no buffer: the next tile's P
             // goes to buf0 meanwhile (every wave is past reading it)
             __syncthreads();
-            if (tn < tend) fetch(tn, buf0);
+            if (tn < tend) fetch(tn, in, buf0);
             step(s + 1, buf1, buf0, B, A, true, false);
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the copy of P, before the stores below
             store(a.out1, A);
@@ -360,7 +366,7 @@ __global__ __launch_bounds__(TXL *NZ, WPS) void k_multi2d(const MultiBatch<N> b)
             if (s < S) step(s, buf0, buf1, A, B, false);
             __syncthreads();
             if (tn < tend) {
-                fetch(tn, buf0);
+                fetch(tn, in, buf0);
                 asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             }
             if (s < S) {
@@ -373,6 +379,7 @@ __global__ __launch_bounds__(TXL *NZ, WPS) void k_multi2d(const MultiBatch<N> b)
         }
         if (tn >= tend) return;
         t = tn;
+        it = in;
     }
 }
 
