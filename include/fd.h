@@ -362,7 +362,7 @@ fd_status fd_check_finite(const fd_state *state, uint32_t *flags, void *stream);
  * states must have begun the same shot and be at the same next step.  With
  * one device per slab this is the per-step halo exchange between
  * neighbouring devices; here both states are on the current device and the
- * planes move by two device-to-device copies on `stream` (2 x 4 planes of
+ * planes move by one copy kernel on `stream` (2 x 4 planes of
  * ny * ceil(nx / 64) * 64 FP32 cells).  Stream-ordered; nothing else is
  * changed. */
 fd_status fd_slab_exchange(const fd_state *upper, const fd_state *lower, void *stream);

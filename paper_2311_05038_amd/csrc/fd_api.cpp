@@ -66,9 +66,9 @@ struct MultiPlan {
     int steps;   // 0: no shape fits, or single steps are not slower
 };
 
-// A single step's time on `cells` padded cells, us (256^2 4.5, 1024^2 7.4,
-// 2048 x 4096 22): the launch, or the fields' 16 bytes per cell.
-double single_us(double cells) { return std::max(4.5, 2.2 + cells * 2.4e-6); }
+// A single step's time on `cells` padded cells, us (256^2 3.4, 1024^2 5.5,
+// 2048 x 4096 22.7): the launch, or the fields' 16 bytes per cell.
+double single_us(double cells) { return 3.2 + cells * 2.35e-6; }
 
 // pairs: launches come in pairs that start and end on the same buffers, so a
 // run is cut into whole pairs of `steps` and a rest of one pair (or of one or
@@ -399,7 +399,7 @@ fd_status fd_create_model(const fd_grid *grid, const float *velocity, void *mode
         void *area = nullptr;
         (void)fdk::routines_scratch(s, &area);
         StepArgs a = base_args(m, nullptr, nullptr);
-        fdk::plan_tiles(a, L.ndim, L.storage, false);
+        fdk::plan_tiles(a, L.ndim, L.storage, fdk::kFwd);
         const fdk::MultiGrid mg{(int)L.nz, L.px};
         if (L.ndim == 2) (void)fdk::multi2d_shape(&mg, 1, 1, nullptr);   // the CU count
         (void)hipGetLastError();
@@ -514,7 +514,7 @@ fd_status fd_shot_graph_create(const fd_model *model, fd_state *state, const fd_
         // occupancy once per storage kind; ask before the capture starts
         int64_t skip = 0;
         StepArgs a = base_args(model, shot, &skip);
-        fdk::plan_tiles(a, model->L.ndim, model->L.storage, false);
+        fdk::plan_tiles(a, model->L.ndim, model->L.storage, fdk::kFwd);
     }
     // The launches are recorded on a private stream (default priority) and
     // replayed on the caller's: the capture itself runs nothing.
@@ -1039,10 +1039,8 @@ fd_status fd_slab_exchange(const fd_state *upper, const fd_state *lower, void *s
     const char *u = (const char *)upper->buf[lvl & 1];
     const char *d = (const char *)lower->buf[lvl & 1];
     hipStream_t s = (hipStream_t)stream;
-    hipError_t e = hipMemcpyAsync((char *)d - kGhost * plane, u + (size_t)(U.nz - kGhost) * plane,
-                                  kGhost * plane, hipMemcpyDeviceToDevice, s);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync((char *)u + (size_t)U.nz * plane, d, kGhost * plane, hipMemcpyDeviceToDevice, s);
+    const hipError_t e = fdk::launch_exchange(u + (size_t)(U.nz - kGhost) * plane, (char *)d - kGhost * plane, d,
+                                              (char *)u + (size_t)U.nz * plane, kGhost * plane, s);
     if (e != hipSuccess) return hip_fail(e, "fd_slab_exchange");
     return ok();
 }

@@ -40,8 +40,9 @@ struct StepArgs {
     const float *gz, *gy, *gx;  // damping profiles (nz, ny, nx entries)
     int32_t nz, ny, nx, px;
     int32_t zc;           // planes (rows in 2D) per block
-    int16_t vx;           // 2D: cells per lane along x (tile width 64 * vx);
-                          // 3D: tile width / 64 (FP32: 4 or 2, the kernel)
+    int16_t vx;           // 2D: rows per thread (0: the streaming kernel);
+                          // 3D: tile width / 64 (FP32: 4, 2, or 1 and 0 for the
+                          // short kernel)
     int16_t zghost;       // 3D FP32: planes of cur readable past each z end (the
                           // ghost planes of a z-slab), else 0 (zero edges)
     int32_t tiles_x, tiles_y, tiles_z;
@@ -92,12 +93,15 @@ struct MultiArgs {
 
 // Layout of the 16-bit storage bookkeeping ("meta", in the state buffer):
 // meta[l] (l < 4) is the exponent of time level l mod 4; the largest
-// magnitude of level l is the maximum over kMaxSlots words at
-// meta[kMaxBase + l * kMaxSlots + k] (float bit patterns; blocks fold their
-// maxima into slot blockIdx % kMaxSlots, which spreads the atomics).
+// magnitude of level l, as far as its exponent goes, is the maximum over the
+// kMaxSlots words meta[slot_word(l, k)] (float bit patterns; blocks fold their
+// maxima into slot blockIdx % kMaxSlots, which spreads the atomics).  The
+// levels' slots are interleaved, so that one level's lie in 8 cache lines:
+// atomics on one line run one after another, 13 ns each with 2 lines a level.
 constexpr int kMaxSlots = 64;
-constexpr int kMaxBase = 16;
+constexpr int kMaxBase = 32;
 constexpr int kMetaWords = kMaxBase + 4 * kMaxSlots;
+constexpr int slot_word(int level, int k) { return kMaxBase + 4 * k + level; }
 // meta[kHealth]: sticky flags of the shot (every storage kind); bit 2 is set
 // when a non-finite value entered it (a wavelet sample times the source
 // amplitude, or a value given to fd_set_wavefield)

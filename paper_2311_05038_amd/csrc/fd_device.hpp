@@ -52,6 +52,29 @@ __device__ __forceinline__ float axis_d2(float m4, float m3, float m2, float m1,
                 fmaf(kA4, m4 + p4, fmaf(kA3, m3 + p3, fmaf(kA2, (m2 - u) + (p2 - u), kA1 * ((m1 - u) + (p1 - u))))));
 }
 
+// The second difference of axis_d2 from the pair sums s4 = u[-4] + u[4],
+// s3 = u[-3] + u[3] and the differences s2 = (u[2] - u) - (u - u[-2]),
+// s1 = (u[1] - u) - (u - u[-1]).
+__device__ __forceinline__ float axis_d2_shared(float s4, float s3, float s2, float s1, float u)
+{
+    return fmaf(kC34, u, fmaf(kA4, s4, fmaf(kA3, s3, fmaf(kA2, s2, kA1 * s1))));
+}
+
+// axis_d2 at the N centres in[4 .. 4 + N) of a run of N + 8 cells.
+template <int N>
+__device__ __forceinline__ void axis_d2_run(const float (&in)[N + 8], float (&out)[N])
+{
+    float d1[N + 1], d2[N + 2];
+#pragma unroll
+    for (int i = 0; i < N + 1; ++i) d1[i] = in[i + 4] - in[i + 3];
+#pragma unroll
+    for (int i = 0; i < N + 2; ++i) d2[i] = in[i + 4] - in[i + 2];
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+        out[i] = axis_d2_shared(in[i] + in[i + 8], in[i + 1] + in[i + 7], d2[i + 2] - d2[i],
+                                d1[i + 1] - d1[i], in[i + 4]);
+}
+
 // new = G (2 cur + c lap) - G^2 prev, evaluated as G (cur + (c lap + (cur -
 // G prev))): the small increment c lap + (cur - G prev) is formed before the
 // large cur is added (G = 1 off the damping band).
@@ -221,7 +244,7 @@ __device__ __forceinline__ float level_max(const int32_t *meta, int la, int lb)
 {
     static_assert(kMaxSlots == 64, "one slot per lane");
     const int lane = threadIdx.x & 63;
-    uint32_t m = max((uint32_t)meta[kMaxBase + la * kMaxSlots + lane], (uint32_t)meta[kMaxBase + lb * kMaxSlots + lane]);
+    uint32_t m = max((uint32_t)meta[slot_word(la, lane)], (uint32_t)meta[slot_word(lb, lane)]);
     for (int off = 32; off >= 1; off >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, off, 64));
     return __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)m));
 }
@@ -245,7 +268,7 @@ __device__ __forceinline__ HalfCtx half_prologue(const StepArgs &a, float inj, b
         if (block0) {
             if (threadIdx.x == 0) a.meta[in] = en;
             // slots of level n+2 (not read by this step) are cleared for the next one
-            if (threadIdx.x < kMaxSlots) a.meta[kMaxBase + iz * kMaxSlots + threadIdx.x] = 0;
+            if (threadIdx.x < kMaxSlots) a.meta[slot_word(iz, threadIdx.x)] = 0;
         }
     }
     return h;
@@ -253,17 +276,18 @@ __device__ __forceinline__ HalfCtx half_prologue(const StepArgs &a, float inj, b
 
 __device__ __forceinline__ int32_t *max_slot(int32_t *meta, int level)
 {
-    return &meta[kMaxBase + level * kMaxSlots + (blockIdx.x & (kMaxSlots - 1))];
+    return &meta[slot_word(level, blockIdx.x & (kMaxSlots - 1))];
 }
 
-// Folds a non-negative float into a slot by atomicMax on its bit pattern
-// (order-independent, hence deterministic).  atomicMax is monotone, so a
-// block whose value does not exceed what the slot already holds may skip
-// the atomic: most blocks do, which keeps the atomics on one slot few.
+// Folds a non-negative float into a slot by atomicMax on its bit pattern.
+// Only the largest magnitude's exponent is ever used (storage_exponent), so a
+// block whose value has no larger exponent than what the slot already holds
+// skips the atomic: most blocks do.  The exponent of the outcome does not
+// depend on the order.
 __device__ __forceinline__ void fold_max(int32_t *slot, float m)
 {
     const uint32_t bits = __float_as_uint(m);
-    if (bits > (uint32_t)__atomic_load_n(slot, __ATOMIC_RELAXED))
+    if ((bits >> 23) > ((uint32_t)__atomic_load_n(slot, __ATOMIC_RELAXED) >> 23))
         atomicMax((unsigned int *)slot, bits);
 }
 

@@ -1,10 +1,11 @@
 // Step kernels and set-up kernels for gfx950 (MI355X).
 //
-// 2D (z, x):  one wave per block.  A block owns a 64*VX-wide column strip and
-//   a chunk of `zc` rows; each lane streams its VX columns down z keeping the
-//   9 rows z-4..z+4 in registers, and the x-neighbours come from one LDS row
-//   (plus 4 halo cells each side).  One HBM read of cur/prev/c and one write
-//   per cell and step (16 B/cell in FP32, 10 B with 16-bit fields).
+// 2D (z, x):  a block of 4 waves loads a tile of 128 columns x 8, 16 or 32 rows
+//   with its halo at once, exchanges it through LDS and updates it (the
+//   largest 16-bit grids: one wave per block streams a 128-column strip down z
+//   with the 9 rows z-4..z+4 in registers).  One read of cur/prev/c and one
+//   write per cell and step (16 B/cell in FP32, 10 B with 16-bit fields).
+//   Several FP32 steps per launch: fd_multi2d.hip.
 // 3D (z, y, x): NW waves per block.  A block owns a tile of the x-y plane
 //   (256x8 cells for FP32 fields, 128x8 for 16-bit) and a chunk of `zc`
 //   planes; lanes stream along z (the slow axis) with a 9-deep register queue
@@ -182,12 +183,14 @@ __device__ __forceinline__ float update(float G, float ctr, float c, float lap, 
 // 2D
 // --------------------------------------------------------------------------
 // CQ: c is read as 16-bit fixed-point codes (16-bit fields, forward step).
+// The streaming 2D step (16-bit fields on the largest grids): one wave takes
+// 64 VX columns and `zc` rows.
 template <int ST, int VX, bool CQ>
 __device__ __forceinline__ void step2d_tile(const StepArgs &a, int tx, int tz,
                                             float (*row)[64 * VX + 8], const HalfCtx &h,
                                             float inj, float &bmax)
 {
-    static_assert(!CQ || ST != kF32, "16-bit c: 16-bit fields");
+    static_assert(ST != kF32, "16-bit fields");
     constexpr int MODE = kFwd;
     using T = typename Stor<ST>::T;
     using CT = std::conditional_t<CQ, uint16_t, float>;
@@ -256,7 +259,6 @@ __device__ __forceinline__ void step2d_tile(const StepArgs &a, int tx, int tz,
     T hv = ld_halo(zb);
     // the row's sponge factor travels with the prefetch: a load issued after
     // it and waited for in the same row would also wait for the prefetch
-    constexpr bool LATE = ST != kF32;   // the 16-bit memory-op order (see top)
     float gn = a.gz[zb];
     Outgoing<T, VX> out;
     out.ok = false;
@@ -276,48 +278,34 @@ __device__ __forceinline__ void step2d_tile(const StepArgs &a, int tx, int tz,
         const float gzp = gn;
         // the previous row's stores go out after the wait for this row's
         // data and just before the next prefetch
-        if constexpr (LATE) {
-            __builtin_amdgcn_sched_barrier(0);
-            flush<T, VX, MODE, false>(out);
-        }
-        if (LATE || z + 1 < ze) {
-            la = ld_cur(z + 5);
-            pv = ld_prev(z + 1);
-            cv = ld_c(z + 1);
-            hv = ld_halo(z + 1);
-            if constexpr (LATE) gn = z + 1 < nz ? a.gz[z + 1] : 0.0f;
-        }
+        __builtin_amdgcn_sched_barrier(0);
+        flush<T, VX, MODE, false>(out);
+        la = ld_cur(z + 5);
+        pv = ld_prev(z + 1);
+        cv = ld_c(z + 1);
+        hv = ld_halo(z + 1);
+        gn = z + 1 < nz ? a.gz[z + 1] : 0.0f;
         float *rw = row[z & 1];
 #pragma unroll
         for (int v = 0; v < VX; ++v) rw[4 + lane * VX + v] = q[4][v];
         if (hlane) rw[hslot] = hc;
         __syncthreads();
-        const float gzz = LATE ? gzp : a.gz[z];
+        const float gzz = gzp;
         float nw[VX], lp[VX], G[VX];
 #pragma unroll
         for (int v = 0; v < VX; ++v) {
             const int li = 4 + lane * VX + v;
-            float lap;
-            if constexpr (ST == kF32) {
-                const float lx = axis_d2(rw[li - 4], rw[li - 3], rw[li - 2], rw[li - 1], q[4][v],
-                                         rw[li + 1], rw[li + 2], rw[li + 3], rw[li + 4]);
-                const float lz = axis_d2(q[0][v], q[1][v], q[2][v], q[3][v], q[4][v], q[5][v],
-                                         q[6][v], q[7][v], q[8][v]);
-                lap = lz + lx;
-            } else {
-                const float lx = stencil_taps(rw[li - 4], rw[li - 3], rw[li - 2], rw[li - 1],
-                                              rw[li + 1], rw[li + 2], rw[li + 3], rw[li + 4]);
-                const float lz = stencil_taps(q[0][v], q[1][v], q[2][v], q[3][v], q[5][v], q[6][v],
-                                              q[7][v], q[8][v]);
-                lap = fmaf(2.0f * kA0, q[4][v], lz + lx);
-            }
+            const float lx = stencil_taps(rw[li - 4], rw[li - 3], rw[li - 2], rw[li - 1],
+                                          rw[li + 1], rw[li + 2], rw[li + 3], rw[li + 4]);
+            const float lz = stencil_taps(q[0][v], q[1][v], q[2][v], q[3][v], q[5][v], q[6][v],
+                                          q[7][v], q[8][v]);
+            const float lap = fmaf(2.0f * kA0, q[4][v], lz + lx);
             G[v] = gzz * gxv[v];
             nw[v] = update<ST>(G[v], q[4][v], cc[v], lap, pc[v], h);
             lp[v] = lap;
         }
         finish_cells<ST, VX, MODE, false, false>(a, h, z, 0, x0, lane_in, (size_t)z * px, (uint32_t)x0, nw,
                                                  lp, pc, cc, G, inj, bmax, out);
-        if constexpr (!LATE) flush<T, VX, MODE, false>(out);
 #pragma unroll
         for (int k = 0; k < 8; ++k)
 #pragma unroll
@@ -338,27 +326,163 @@ __global__ __launch_bounds__(64) void k_step2d(StepArgs a)
     const HalfCtx h = half_prologue<ST>(a, inj, blockIdx.x == 0);
     float bmax = 0.0f;
     step2d_tile<ST, VX, CQ>(a, tx, tz, row, h, inj, bmax);
+    block_max_to<64>(max_slot(a.meta, (int)((a.n + 1) & 3)), bmax * h.sn, nullptr);
+}
+
+// One 2D step with every load of a block's tile in flight at once.  A block
+// owns 128 columns x 8 RZ rows (a thread 4 columns x RZ rows); P with its halo
+// of 4 cells goes to LDS, one barrier, and the update follows.  (A wave that
+// streams down a strip row by row, as in the kernel above, waits about 0.5 us
+// of memory latency per row on grids too small for many waves.  Per step:
+// FP32 256^2 4.5 -> 3.4 us, 1024^2 7.8 -> 5.4, 1201 x 1747 10.5 -> 8.6, 2048 x
+// 4096 23.9 -> 22.7; BF16 256^2 7.6 -> 5.2, 1024^2 12.5 -> 7.3, 1201 x 1747
+// 12.8 -> 9.4.)
+template <int ST, int RZ, bool CQ>
+__device__ __forceinline__ void step2d_block(const StepArgs &a, int tx, int tz, float *pl, bool block0, int32_t *red)
+{
+    using T = typename Stor<ST>::T;
+    using CT = std::conditional_t<CQ, uint16_t, float>;
+    using PT = Pack<T, 4>;
+    constexpr int TX = 128, TZ = 8 * RZ, LW = TX + 8;
+    const int lx = threadIdx.x & 31, lg = threadIdx.x >> 5;
+    const int xb = tx * TX, zb = tz * TZ, x0 = xb + 4 * lx, z0 = zb + RZ * lg;
+    const int nx = a.nx, nz = a.nz, pxi = a.px;
+    const size_t px = (size_t)pxi;
+    const T *__restrict__ cur = (const T *)a.cur;
+    const T *__restrict__ prv = (const T *)a.prev;
+    const CT *cb;
+    if constexpr (CQ)
+        cb = a.c16;
+    else
+        cb = a.c;
+    const bool xin = x0 < pxi;
+    PT own[RZ], pv[RZ], zh{}, xh{};
+    Pack<CT, 4> cv[RZ];
+#pragma unroll
+    for (int r = 0; r < RZ; ++r) {
+        own[r] = PT{};
+        if (xin && z0 + r < nz) own[r] = ldp<T, 4>(cur + (size_t)(z0 + r) * px + x0);
+    }
+    // halo rows: one 4-cell unit a thread; halo columns: one for 2 TZ threads
+    const int hrow = lg < 4 ? lg - 4 : TZ + lg - 4, hz = zb + hrow;
+    if (xin && hz >= 0 && hz < nz) zh = ldp<T, 4>(cur + (size_t)hz * px + x0);
+    const int crow = threadIdx.x >> 1, cx = threadIdx.x & 1 ? xb + TX : xb - 4;
+    const bool cl = threadIdx.x < 2 * TZ;
+    if (cl && zb + crow < nz && cx >= 0 && cx < pxi) xh = ldp<T, 4>(cur + (size_t)(zb + crow) * px + cx);
+#pragma unroll
+    for (int r = 0; r < RZ; ++r) {
+        pv[r] = PT{};
+        cv[r] = Pack<CT, 4>{};
+        if (xin && z0 + r < nz) {
+            pv[r] = ldp<T, 4>(prv + (size_t)(z0 + r) * px + x0);
+            cv[r] = ldp<CT, 4>(cb + (size_t)(z0 + r) * px + x0);
+        }
+    }
+    float gx[4], gz[RZ];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) gx[v] = x0 + v < nx ? a.gx[x0 + v] : 0.0f;
+#pragma unroll
+    for (int r = 0; r < RZ; ++r) gz[r] = z0 + r < nz ? a.gz[z0 + r] : 0.0f;
+    float inj = 0.0f;
+    if (a.n + 1 < a.nt) inj = a.amp * a.wavelet[a.n + 1];
+    const HalfCtx h = half_prologue<ST>(a, inj, block0);
+
+    auto put = [&](int at_l, const PT &p) {
+        Pack<float, 4> o;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) o.v[v] = decode_raw<ST>(p.v[v]);
+        stp<float, 4>(pl + at_l, o);
+    };
+    const int li = (RZ * lg + 4) * LW + 4 + 4 * lx;
+#pragma unroll
+    for (int r = 0; r < RZ; ++r) put(li + r * LW, own[r]);
+    put((hrow + 4) * LW + 4 + 4 * lx, zh);
+    if (cl) put((crow + 4) * LW + (threadIdx.x & 1 ? 4 + TX : 0), xh);
+    __syncthreads();
+
+    float col[RZ + 8][4];
+#pragma unroll
+    for (int k = 0; k < RZ + 8; ++k) {
+        const Pack<float, 4> p = ldp<float, 4>(pl + li + (k - 4) * LW);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) col[k][v] = p.v[v];
+    }
+    float lzz[RZ][4];
+    if constexpr (ST == kF32) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            float in[RZ + 8], out[RZ];
+#pragma unroll
+            for (int k = 0; k < RZ + 8; ++k) in[k] = col[k][v];
+            axis_d2_run<RZ>(in, out);
+#pragma unroll
+            for (int r = 0; r < RZ; ++r) lzz[r][v] = out[r];
+        }
+    }
+    float bmax = 0.0f;
+#pragma unroll
+    for (int r = 0; r < RZ; ++r) {
+        const Pack<float, 4> pl4 = ldp<float, 4>(pl + li + r * LW - 4), pr4 = ldp<float, 4>(pl + li + r * LW + 4);
+        float row[12], nw[4], lp[4], G[4], pc[4], cc[4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            row[v] = pl4.v[v];
+            row[4 + v] = col[4 + r][v];
+            row[8 + v] = pr4.v[v];
+            pc[v] = decode_raw<ST>(pv[r].v[v]);
+            if constexpr (CQ)
+                cc[v] = (float)cv[r].v[v] * a.c16_scale;   // exact: a power-of-two scale
+            else
+                cc[v] = cv[r].v[v];
+            G[v] = gz[r] * gx[v];
+        }
+        float lxx[4];
+        if constexpr (ST == kF32) axis_d2_run<4>(row, lxx);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const float u = col[4 + r][v];
+            float lap;
+            if constexpr (ST == kF32) {
+                lap = lzz[r][v] + lxx[v];
+            } else {
+                const float lx8 = stencil_taps(row[v], row[v + 1], row[v + 2], row[v + 3], row[v + 5], row[v + 6],
+                                               row[v + 7], row[v + 8]);
+                const float lz8 = stencil_taps(col[r][v], col[r + 1][v], col[r + 2][v], col[r + 3][v], col[r + 5][v],
+                                               col[r + 6][v], col[r + 7][v], col[r + 8][v]);
+                lap = fmaf(2.0f * kA0, u, lz8 + lx8);
+            }
+            nw[v] = update<ST>(G[v], u, cc[v], lap, pc[v], h);
+            lp[v] = lap;
+        }
+        Outgoing<T, 4> out;
+        finish_cells<ST, 4, kFwd, false, false>(a, h, z0 + r, 0, x0, xin && z0 + r < nz, (size_t)(z0 + r) * px,
+                                                (uint32_t)x0, nw, lp, pc, cc, G, inj, bmax, out);
+        flush<T, 4, kFwd, false>(out);
+    }
     if constexpr (ST != kF32)
-        block_max_to<64>(max_slot(a.meta, (int)((a.n + 1) & 3)), bmax * h.sn, nullptr);
+        block_max_to<256>(max_slot(a.meta, (int)((a.n + 1) & 3)), bmax * h.sn, (float *)red);
+}
+
+template <int ST, int RZ, bool CQ>
+__global__ __launch_bounds__(256) void k_step2d_block(StepArgs a)
+{
+    __shared__ __attribute__((aligned(16))) float pl[(8 * RZ + 8) * 136];
+    __shared__ int32_t red[4];
+    const int t = xcd_tile(blockIdx.x, a.tiles_x * a.tiles_z);
+    step2d_block<ST, RZ, CQ>(a, t % a.tiles_x, t / a.tiles_x, pl, blockIdx.x == 0, red);
 }
 
 // Batched 2D FP32 step: block b belongs to the item whose tile range holds
 // b; every item keeps its own grid, fields and step index.
-template <int VX>
-__global__ __launch_bounds__(64) void k_step2d_batch(Batch2D b)
+__global__ __launch_bounds__(256) void k_step2d_batch(Batch2D b)
 {
-    __shared__ float row[2][64 * VX + 8];
+    __shared__ __attribute__((aligned(16))) float pl[(8 + 8) * 136];
     const int t = blockIdx.x;
     int i = 0;
     while (i + 1 < b.count && t >= b.begin[i + 1]) ++i;
     const StepArgs &a = b.it[i];
     const int lt = t - b.begin[i];
-    const int tx = lt % a.tiles_x, tz = lt / a.tiles_x;
-    float inj = 0.0f;
-    if (a.n + 1 < a.nt) inj = a.amp * a.wavelet[a.n + 1];
-    const HalfCtx h{1.0f, 1.0f, 1.0f, 1.0f};
-    float bmax = 0.0f;
-    step2d_tile<kF32, VX, false>(a, tx, tz, row, h, inj, bmax);
+    step2d_block<kF32, 1, false>(a, lt % a.tiles_x, lt / a.tiles_x, pl, false, nullptr);
 }
 
 // --------------------------------------------------------------------------
@@ -658,6 +782,153 @@ __global__ __launch_bounds__(64 * NW) void k_step3d(StepArgs a)
 }
 
 // --------------------------------------------------------------------------
+// 3D, FP32, grids too small to fill the device with long chunks
+// --------------------------------------------------------------------------
+constexpr int kShortTX = 64, kShortTY = 16;   // 16 lanes of 4 cells x 16 rows
+
+// The streaming kernel above keeps one plane of loads in flight per wave: on a
+// grid whose chunks are a few planes long it spends a memory latency on every
+// plane and eight on priming its queue (96 x 120 x 152: 12.5 us for 28 MB).
+// Here a block owns 64 x 16 cells of ZC planes and issues every load of them
+// at once: 8 + ZC planes of P, ZC of Pold and c and the x and y halos, 16
+// bytes a lane; the ZC planes then go to LDS, one barrier, and the update
+// follows.  P is read (8 + ZC) / ZC + 1/2 + 1/8 times, so blocks are dealt x
+// first, then z: the z neighbours that read the same planes run at the same
+// time on one XCD and find them in its L2 (y before z: 201 x 333 x 289 72
+// against 58 us).  Per step, streaming / this: 64^3 8.2 / 5.0 us, 96 x 120 x
+// 152 12.5 / 11.2, 78 x 259 x 333 30.0 / 26.5, 201 x 333 x 289 66 / 58;
+// adjoint 96 x 120 x 152 14.6 / 12.7, 201 x 333 x 289 108 / 92.  Arithmetic and
+// results are those of k_step3d.  NTS: Pold, c and the new level bypass the
+// caches (grids beyond the Infinity Cache).
+template <int ZC, int MODE, bool NTS>
+__global__ __launch_bounds__(256) void k_step3d_short(StepArgs a)
+{
+    constexpr int TX = kShortTX, TY = kShortTY, LW = TX + 8, LH = TY + 8, NT = 16 * TY;
+    // 16-byte loads of the y halo (8 rows a plane) and of the x halo (2 a row)
+    constexpr int YT = 8 * ZC * 16, XT = TY * ZC * 2;
+    constexpr int YH = (YT + NT - 1) / NT, XH = (XT + NT - 1) / NT;
+    __shared__ __attribute__((aligned(16))) float pl[ZC][LH * LW];
+    const int lx = threadIdx.x & 15, ly = threadIdx.x >> 4;
+    const int t = xcd_tile(blockIdx.x, a.tiles_x * a.tiles_y * a.tiles_z);
+    const int tx = t % a.tiles_x, t2 = t / a.tiles_x, tz = t2 % a.tiles_z, ty = t2 / a.tiles_z;
+    const int xb = tx * TX, yb = ty * TY, zb = tz * ZC, x0 = xb + 4 * lx, y = yb + ly;
+    const int nx = a.nx, ny = a.ny, nz = a.nz, zlo = -a.zghost, zhi = nz + a.zghost;
+    const size_t px = (size_t)a.px, pp = (size_t)ny * px;
+    const bool in = x0 < a.px && y < ny;
+    const float *cur = (const float *)a.cur, *prv = (const float *)a.prev;
+    using P4 = Pack<float, 4>;
+    auto load = [&](const float *f, int z, int yy, int xx, bool ok) -> P4 {
+        P4 p{};
+        if (ok) p = ldp<float, 4>(f + (ptrdiff_t)z * (ptrdiff_t)pp + (size_t)yy * px + xx);
+        return p;
+    };
+    P4 q[ZC + 8], pv[ZC], cv[ZC], yh[YH], xh[XH];
+    int ys[YH], xs[XH];
+#pragma unroll
+    for (int k = 0; k < ZC + 8; ++k) {
+        const int z = zb - 4 + k;
+        q[k] = load(cur, z, y, x0, in && z >= zlo && z < zhi);
+    }
+#pragma unroll
+    for (int k = 0; k < YH; ++k) {
+        const int u = k * NT + (int)threadIdx.x, zz = u / 128, r = (u >> 4) & 7, xx = xb + 4 * (u & 15);
+        const int row = r < 4 ? r : TY + r, yy = yb + row - 4;   // row of the LDS plane
+        yh[k] = load(cur, zb + zz, yy, xx, u < YT && xx < a.px && yy >= 0 && yy < ny && zb + zz < nz);
+        ys[k] = u < YT ? zz * LH * LW + row * LW + 4 + 4 * (u & 15) : -1;
+    }
+#pragma unroll
+    for (int k = 0; k < XH; ++k) {
+        const int u = k * NT + (int)threadIdx.x, zz = u / (2 * TY), r = (u >> 1) % TY, side = u & 1;
+        const int xx = side ? xb + TX : xb - 4, yy = yb + r;
+        xh[k] = load(cur, zb + zz, yy, xx, u < XT && xx >= 0 && xx < a.px && yy < ny && zb + zz < nz);
+        xs[k] = u < XT ? zz * LH * LW + (r + 4) * LW + (side ? 4 + TX : 0) : -1;
+    }
+#pragma unroll
+    for (int k = 0; k < ZC; ++k) {
+        pv[k] = P4{};
+        cv[k] = P4{};
+        if (in && zb + k < nz) {
+            const size_t e = (size_t)(zb + k) * pp + (size_t)y * px + x0;
+            pv[k] = NTS ? ldp_stream<float, 4>(prv + e) : ldp<float, 4>(prv + e);
+            cv[k] = NTS ? ldp_stream<float, 4>(a.c + e) : ldp<float, 4>(a.c + e);
+        }
+    }
+    float gx[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) gx[v] = x0 + v < nx ? a.gx[x0 + v] : 0.0f;
+    const float gy = y < ny ? a.gy[y] : 0.0f;
+    float gz[ZC];
+#pragma unroll
+    for (int k = 0; k < ZC; ++k) gz[k] = zb + k < nz ? a.gz[zb + k] : 0.0f;
+    float inj = 0.0f;
+    if constexpr (MODE != kAdj)
+        if (a.n + 1 < a.nt) inj = a.amp * a.wavelet[a.n + 1];
+
+    float *base = &pl[0][0];
+    const int li = (ly + 4) * LW + 4 + 4 * lx;
+#pragma unroll
+    for (int k = 0; k < ZC; ++k) stp<float, 4>(pl[k] + li, q[k + 4]);
+#pragma unroll
+    for (int k = 0; k < YH; ++k)
+        if (ys[k] >= 0) stp<float, 4>(base + ys[k], yh[k]);
+#pragma unroll
+    for (int k = 0; k < XH; ++k)
+        if (xs[k] >= 0) stp<float, 4>(base + xs[k], xh[k]);
+    __syncthreads();
+
+    float lz[ZC][4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        float col[ZC + 8], out[ZC];
+#pragma unroll
+        for (int k = 0; k < ZC + 8; ++k) col[k] = q[k].v[v];
+        axis_d2_run<ZC>(col, out);
+#pragma unroll
+        for (int k = 0; k < ZC; ++k) lz[k][v] = out[k];
+    }
+    const HalfCtx h{1.0f, 1.0f, 1.0f, 1.0f};
+    float bmax = 0.0f;
+#pragma unroll
+    for (int k = 0; k < ZC; ++k) {
+        const int z = zb + k;
+        if (z >= nz) break;
+        const float *P = pl[k] + li;
+        const P4 xl = ldp<float, 4>(P - 4), xr = ldp<float, 4>(P + 4);
+        P4 r[8];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            r[e] = ldp<float, 4>(P + (e - 4) * LW);
+            r[4 + e] = ldp<float, 4>(P + (e + 1) * LW);
+        }
+        float row[12], lxx[4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            row[v] = xl.v[v];
+            row[4 + v] = q[k + 4].v[v];
+            row[8 + v] = xr.v[v];
+        }
+        axis_d2_run<4>(row, lxx);
+        float nw[4], lp[4], G[4], pc[4], cc[4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const float u = q[k + 4].v[v];
+            const float lyy = axis_d2(r[0].v[v], r[1].v[v], r[2].v[v], r[3].v[v], u, r[4].v[v], r[5].v[v],
+                                      r[6].v[v], r[7].v[v]);
+            const float lap = lz[k][v] + (lyy + lxx[v]);
+            pc[v] = pv[k].v[v];
+            cc[v] = cv[k].v[v];
+            G[v] = (gz[k] * gy) * gx[v];
+            nw[v] = leapfrog(G[v], u, cc[v], lap, pc[v]);
+            lp[v] = MODE == kAdj ? u : lap;
+        }
+        Outgoing<float, 4> out;
+        finish_cells<kF32, 4, MODE, NTS, false>(a, h, z, y, x0, in, (size_t)z * pp + (size_t)y * px, (uint32_t)x0,
+                                                  nw, lp, pc, cc, G, inj, bmax, out);
+        flush<float, 4, MODE, NTS>(out);
+    }
+}
+
+// --------------------------------------------------------------------------
 // Set-up and utility kernels
 // --------------------------------------------------------------------------
 __global__ void k_fill_u32(uint32_t *p, size_t n, uint32_t val)
@@ -754,7 +1025,7 @@ __global__ void k_begin(void *cur, int64_t src_off, float amp, const float *wave
         const int e0 = storage_exponent(fabsf(x0));
         ((T *)cur)[src_off] = encode<ST>(x0, pow2i(-e0));
         meta[0] = e0;
-        meta[kMaxBase] = (int32_t)__float_as_uint(fabsf(x0));
+        meta[slot_word(0, 0)] = (int32_t)__float_as_uint(fabsf(x0));
     }
 }
 
@@ -770,17 +1041,18 @@ __global__ void k_get_field(const void *buf, float *__restrict__ out, int64_t nr
     });
 }
 
-// max |x| over a dense array, folded into slots[blockIdx % kMaxSlots] as
-// float bits.
-__global__ void k_absmax(const float *__restrict__ x, size_t n, uint32_t *slots)
+// Clears a level's magnitude slots.
+__global__ void k_clear_level(int32_t *meta, int32_t level) { meta[slot_word(level, threadIdx.x)] = 0; }
+
+// max |x| over a dense array, folded into a level's magnitude slots.
+__global__ void k_absmax(const float *__restrict__ x, size_t n, int32_t *meta, int32_t level)
 {
-    uint32_t *slot = &slots[blockIdx.x & (kMaxSlots - 1)];
     float m = 0.0f;
     size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     const size_t stride = (size_t)gridDim.x * blockDim.x;
     for (; i < n; i += stride) m = fmaxf(m, fabsf(x[i]));
     for (int off = 32; off >= 1; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
-    if ((threadIdx.x & 63) == 0) atomicMax(slot, __float_as_uint(m));
+    if ((threadIdx.x & 63) == 0) fold_max(max_slot(meta, level), m);
 }
 
 // Dense FP32 -> padded stored field; 16-bit storage takes its exponent from
@@ -804,6 +1076,22 @@ __global__ void k_set_field(const float *__restrict__ in, void *buf, int64_t nro
     });
     // a non-finite value set into the shot is recorded in its health flags
     if (__ballot(bad) != 0 && (threadIdx.x & 63) == 0) atomicOr((uint32_t *)&meta[kHealth], kNonfiniteInput);
+}
+
+// The two copies of a ghost exchange in one launch: n16 16-byte words from
+// u_own to d_ghost and from d_own to u_ghost.  (Two device-to-device copies
+// cost 13 us a step of three small slabs; this kernel about 4 an exchange.)
+__global__ __launch_bounds__(256) void k_exchange(const uint4 *__restrict__ u_own, uint4 *__restrict__ d_ghost,
+                                                  const uint4 *__restrict__ d_own, uint4 *__restrict__ u_ghost,
+                                                  size_t n16)
+{
+    size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const size_t stride = (size_t)gridDim.x * blockDim.x;
+    for (; i < n16; i += stride) {
+        const uint4 a = u_own[i], b = d_own[i];
+        d_ghost[i] = a;
+        u_ghost[i] = b;
+    }
 }
 
 // Sets `bit` in *flags when a stored level holds a non-finite value (NaN or
@@ -917,11 +1205,11 @@ hipError_t launch_set_field(int storage, const float *in, void *buf, int64_t nro
                             int32_t px, int32_t *meta, int32_t slot, hipStream_t s)
 {
     if (storage != kF32) {
-        uint32_t *slots = (uint32_t *)&meta[kMaxBase + slot * kMaxSlots];
-        hipError_t e = launch_fill_u32(slots, kMaxSlots, 0u, s);
+        hipLaunchKernelGGL(k_clear_level, dim3(1), dim3(kMaxSlots), 0, s, meta, slot);
+        hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL(k_absmax, dim3(grid_blocks((size_t)nrows * nx, 256)), dim3(256), 0, s,
-                           in, (size_t)nrows * nx, slots);
+                           in, (size_t)nrows * nx, meta, slot);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -931,6 +1219,17 @@ hipError_t launch_set_field(int storage, const float *in, void *buf, int64_t nro
     case kF16: hipLaunchKernelGGL(k_set_field<kF16>, g, b, 0, s, in, buf, nrows, nx, px, meta, slot); break;
     default: hipLaunchKernelGGL(k_set_field<kBF16>, g, b, 0, s, in, buf, nrows, nx, px, meta, slot); break;
     }
+    return hipGetLastError();
+}
+
+hipError_t launch_exchange(const void *u_own, void *d_ghost, const void *d_own, void *u_ghost, size_t bytes,
+                           hipStream_t s)
+{
+    if (bytes % 16 != 0) return hipErrorInvalidValue;
+    const size_t n16 = bytes / 16;
+    if (n16 == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_exchange, dim3(grid_blocks(n16, 256)), dim3(256), 0, s, (const uint4 *)u_own,
+                       (uint4 *)d_ghost, (const uint4 *)d_own, (uint4 *)u_ghost, n16);
     return hipGetLastError();
 }
 
@@ -998,7 +1297,6 @@ hipError_t launch_grad_finish(const double *g, const float *c, double *grad_v, i
 #endif
 constexpr int k3dVX32 = FD_3D_VX32, k3dRY32 = FD_3D_RY32;   // FP32 fields
 constexpr int k3dVX16 = FD_3D_VX16, k3dRY16 = FD_3D_RY16;   // 16-bit fields
-constexpr int kBatchVX = 2;
 
 // FP32 fields have two tile shapes: 256x8 (4 cells x 2 rows per lane, 2
 // waves per SIMD) and 128x8 (4 cells x 1 row per lane, two rows per wave, 3
@@ -1063,26 +1361,51 @@ static int64_t resident_blocks_3d(int storage, bool cq, bool narrow)
 // zc planes (the defaults come from a sweep of shapes on the 512^3 and
 // 768x768x512 grids; FP32 grids pick the wide or the narrow tile with
 // narrow_tile_f32).
-// 2D: one wave, 64 VX columns by zc rows; the widest tile and tallest chunk
-// that still give >= 2048 blocks (8 per CU) are taken from
-// (VX, zc) = (2, 16), (2, 8), (1, 8), (1, 4).
-void plan_tiles(StepArgs &a, int ndim, int storage, bool batched)
+// 2D: blocks of 128 columns by 8 RZ rows.  FP32 fields take RZ = 1 everywhere
+// (RZ = 2 and 4 within 3% where they are faster: 1024^2 5.6 / 5.4 / 5.8 us,
+// 2048 x 4096 22.7 / 23.3 / 25.1).  16-bit blocks each read the 128 magnitude
+// words and fold a maximum, so larger blocks pay earlier (BF16, RZ = 1 / 2 / 4:
+// 512^2 5.4 / 5.8 / 7.1 us, 1024^2 8.2 / 7.2 / 7.7, 1201 x 1747 13.0 / 9.3 /
+// 9.6, 2048^2 19.6 / 14.6 / 11.8), and above 1536 blocks of RZ = 4 the
+// streaming kernel with chunks of 16 rows is kept (2048 x 4096 binary16 23.1
+// us against 26.2, with 16-bit c 22.1 against 24.8).
+//
+// 3D FP32 also has the short kernel (k_step3d_short).  It is the faster one on
+// every measured grid up to 2^24.4 padded cells, whose fields (12 B per cell)
+// fit the 256 MB Infinity Cache (256^3 49-51 us against 50-54, 64 x 512^2 48
+// against 51, 128 x 512^2 102 against 96), with 2 planes per block below 12 M
+// cells and 4 above (100 x 200 x 300 23.0 / 23.8 us, 201 x 333 x 289 61.5 /
+// 58).  Beyond, with accesses that bypass the caches, it stays ahead for the
+// adjoint step (384^3 239 against 260 us, 512^3 560 against 562) and where
+// the streaming tiles are mostly padding (300^3 87 against 94).
+void plan_tiles(StepArgs &a, int ndim, int storage, int mode)
 {
     if (ndim == 2) {
-        static const int cand[4][2] = {{2, 16}, {2, 8}, {1, 8}, {1, 4}};
-        for (int i = 0; i < 4; ++i) {
-            if (batched && cand[i][0] != kBatchVX) continue;  // the batched kernel's width only
-            a.vx = cand[i][0];
-            a.zc = cand[i][1];
-            a.tiles_x = (a.nx + 64 * a.vx - 1) / (64 * a.vx);
-            a.tiles_z = (a.nz + a.zc - 1) / a.zc;
-            if ((int64_t)a.tiles_x * a.tiles_z >= 2048) break;
-        }
+        // a.vx records RZ (0: the streaming kernel)
+        a.tiles_x = (a.px + 127) / 128;
         a.tiles_y = 1;
+        auto blocks = [&](int rz) { return (int64_t)a.tiles_x * ((a.nz + 8 * rz - 1) / (8 * rz)); };
+        a.vx = storage == kF32 || blocks(1) <= 320 ? 1 : blocks(2) <= 1100 ? 2 : blocks(4) <= 1536 ? 4 : 0;
+        a.zc = a.vx ? 8 * a.vx : 16;
+        a.tiles_z = (a.nz + a.zc - 1) / a.zc;
     } else {
         // 3D: a.vx records the tile width in units of 64 cells, which picks
-        // the FP32 kernel (4: 256 wide, 2: 128 wide)
+        // the FP32 kernel (4: 256 wide, 2: 128 wide; the short kernel: 1, or 0
+        // with accesses that bypass the caches)
         const bool narrow = storage == kF32 && narrow_tile_f32(a.nx, a.ny, a.nz);
+        if (storage == kF32) {
+            const int64_t cells = (int64_t)a.px * a.ny * a.nz;
+            const int64_t tile = narrow ? k3dTXN32 : k3dTXW32, width = (a.nx + tile - 1) / tile * tile;
+            const bool cached = cells <= 22000000;
+            if (cached || mode == kAdj || 100 * width > 115 * a.px) {
+                a.vx = cached ? 1 : 0;
+                a.zc = cells <= 12000000 ? 2 : 4;
+                a.tiles_x = (a.px + kShortTX - 1) / kShortTX;
+                a.tiles_y = (a.ny + kShortTY - 1) / kShortTY;
+                a.tiles_z = (a.nz + a.zc - 1) / a.zc;
+                return;
+            }
+        }
         const int VX = storage == kF32 ? k3dVX32 : k3dVX16;
         const int RY = storage == kF32 ? (narrow ? k3dRYN32 : k3dRY32) : k3dRY16;
         const int NW = storage == kF32 ? FD_3D_NW32 : FD_3D_NW16;
@@ -1123,31 +1446,36 @@ template <int ST, int MODE, bool CQ = false>
 static void launch3d(const StepArgs &a, int nb, hipStream_t s)
 {
     if constexpr (ST == kF32) {
-        if (a.vx * 64 == k3dTXN32)
-            hipLaunchKernelGGL((k_step3d<ST, k3dVX32, k3dRYN32, FD_3D_NW32, k3dRPWN32, MODE, false>), dim3(nb),
-                               dim3(64 * FD_3D_NW32), 0, s, a);
-        else
-            hipLaunchKernelGGL((k_step3d<ST, k3dVX32, k3dRY32, FD_3D_NW32, FD_3D_RPW32, MODE, false>), dim3(nb),
-                               dim3(64 * FD_3D_NW32), 0, s, a);
+        if (a.vx == 1 && a.zc == 2)
+            hipLaunchKernelGGL((k_step3d_short<2, MODE, false>), dim3(nb), dim3(256), 0, s, a);
+        else if (a.vx == 1)
+            hipLaunchKernelGGL((k_step3d_short<4, MODE, false>), dim3(nb), dim3(256), 0, s, a);
+        else if (a.vx == 0 || MODE == kAdj)   // (the plan gives the adjoint no other)
+            hipLaunchKernelGGL((k_step3d_short<4, MODE, true>), dim3(nb), dim3(256), 0, s, a);
+        else if constexpr (MODE != kAdj) {
+            if (a.vx * 64 == k3dTXN32)
+                hipLaunchKernelGGL((k_step3d<ST, k3dVX32, k3dRYN32, FD_3D_NW32, k3dRPWN32, MODE, false>), dim3(nb),
+                                   dim3(64 * FD_3D_NW32), 0, s, a);
+            else
+                hipLaunchKernelGGL((k_step3d<ST, k3dVX32, k3dRY32, FD_3D_NW32, FD_3D_RPW32, MODE, false>), dim3(nb),
+                                   dim3(64 * FD_3D_NW32), 0, s, a);
+        }
     }
     else
         hipLaunchKernelGGL((k_step3d<ST, k3dVX16, k3dRY16, FD_3D_NW16, FD_3D_RPW16, MODE, CQ>), dim3(nb),
                            dim3(64 * FD_3D_NW16), 0, s, a);
 }
 
-template <int VX>
-static void launch2d(const StepArgs &a, int storage, int nb, hipStream_t s)
+template <int ST, bool CQ>
+static void launch2d(const StepArgs &a, int nb, hipStream_t s)
 {
-    const dim3 g(nb), b(64);
-    const bool cq = a.c16 != nullptr;
-    if (storage == kF32) {
-        hipLaunchKernelGGL((k_step2d<kF32, VX, false>), g, b, 0, s, a);
-    } else if (storage == kF16) {
-        if (cq) hipLaunchKernelGGL((k_step2d<kF16, VX, true>), g, b, 0, s, a);
-        else hipLaunchKernelGGL((k_step2d<kF16, VX, false>), g, b, 0, s, a);
+    if constexpr (ST == kF32) {
+        hipLaunchKernelGGL((k_step2d_block<ST, 1, CQ>), dim3(nb), dim3(256), 0, s, a);
     } else {
-        if (cq) hipLaunchKernelGGL((k_step2d<kBF16, VX, true>), g, b, 0, s, a);
-        else hipLaunchKernelGGL((k_step2d<kBF16, VX, false>), g, b, 0, s, a);
+        if (a.vx == 1) hipLaunchKernelGGL((k_step2d_block<ST, 1, CQ>), dim3(nb), dim3(256), 0, s, a);
+        else if (a.vx == 2) hipLaunchKernelGGL((k_step2d_block<ST, 2, CQ>), dim3(nb), dim3(256), 0, s, a);
+        else if (a.vx == 4) hipLaunchKernelGGL((k_step2d_block<ST, 4, CQ>), dim3(nb), dim3(256), 0, s, a);
+        else hipLaunchKernelGGL((k_step2d<ST, 2, CQ>), dim3(nb), dim3(64), 0, s, a);
     }
 }
 
@@ -1157,11 +1485,15 @@ hipError_t launch_step(StepArgs a, int ndim, int storage, int mode, hipStream_t 
     if (a.c16 != nullptr && (storage == kF32 || mode != kFwd)) return hipErrorInvalidValue;
     // the history and adjoint modes in 2D are launch_multi2d's
     if (ndim == 2 && mode != kFwd) return hipErrorInvalidValue;
-    plan_tiles(a, ndim, storage, false);
+    plan_tiles(a, ndim, storage, mode);
     const int nb = a.tiles_x * a.tiles_y * a.tiles_z;
     if (ndim == 2) {
-        if (a.vx == 2) launch2d<2>(a, storage, nb, s);
-        else launch2d<1>(a, storage, nb, s);
+        const bool cq = a.c16 != nullptr;
+        if (storage == kF32) launch2d<kF32, false>(a, nb, s);
+        else if (storage == kF16 && cq) launch2d<kF16, true>(a, nb, s);
+        else if (storage == kF16) launch2d<kF16, false>(a, nb, s);
+        else if (cq) launch2d<kBF16, true>(a, nb, s);
+        else launch2d<kBF16, false>(a, nb, s);
     } else {
         if (storage == kF32) {
             if (mode == kFwd) launch3d<kF32, kFwd>(a, nb, s);
@@ -1182,13 +1514,13 @@ hipError_t launch_step_batch2d(Batch2D &b, hipStream_t s)
 {
     int total = 0;
     for (int i = 0; i < b.count; ++i) {
-        plan_tiles(b.it[i], 2, kF32, true);
+        plan_tiles(b.it[i], 2, kF32, kFwd);
         b.begin[i] = total;
         total += b.it[i].tiles_x * b.it[i].tiles_z;
     }
     b.begin[b.count] = total;
     if (total == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_step2d_batch<kBatchVX>, dim3(total), dim3(64), 0, s, b);
+    hipLaunchKernelGGL(k_step2d_batch, dim3(total), dim3(256), 0, s, b);
     return hipGetLastError();
 }
 

@@ -18,9 +18,8 @@ struct Batch2D {
 };
 static_assert(sizeof(Batch2D) <= 4096, "batched step arguments must fit the kernel-argument segment");
 
-// Fills tiles_x/y/z, zc and vx of `a` for the kernel variant that runs it
-// (batched: the tile width of the batched 2D kernel).
-void plan_tiles(StepArgs &a, int ndim, int storage, bool batched);
+// Fills tiles_x/y/z, zc and vx of `a` for the kernel variant that runs it.
+void plan_tiles(StepArgs &a, int ndim, int storage, int mode);
 
 // The same for launches of several 2D FP32 steps (one item: a lone shot).
 template <int N>
@@ -74,6 +73,10 @@ hipError_t launch_get_field(int storage, const void *buf, float *out, int64_t nr
                             int32_t px, const int32_t *meta, int32_t level_slot, hipStream_t s);
 hipError_t launch_set_field(int storage, const float *in, void *buf, int64_t nrows, int32_t nx,
                             int32_t px, int32_t *meta, int32_t slot, hipStream_t s);
+// `bytes` (a multiple of 16) from u_own to d_ghost and from d_own to u_ghost,
+// all 16-byte aligned.
+hipError_t launch_exchange(const void *u_own, void *d_ghost, const void *d_own, void *u_ghost, size_t bytes,
+                           hipStream_t s);
 // Sets `bit` in *flags if the `bytes` (a multiple of 16) of a stored level
 // at `level` (16-byte aligned) hold a non-finite value; with `health`, also
 // the shot's sticky non-finite-input flag.

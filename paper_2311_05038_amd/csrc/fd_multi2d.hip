@@ -38,29 +38,6 @@
 
 namespace fdk {
 
-// The second difference of axis_d2 from the pair sums s4 = u[-4] + u[4],
-// s3 = u[-3] + u[3] and the differences s2 = (u[2] - u) - (u - u[-2]),
-// s1 = (u[1] - u) - (u - u[-1]).
-__device__ __forceinline__ float axis_d2_shared(float s4, float s3, float s2, float s1, float u)
-{
-    return fmaf(kC34, u, fmaf(kA4, s4, fmaf(kA3, s3, fmaf(kA2, s2, kA1 * s1))));
-}
-
-// axis_d2 at the N centres in[4 .. 4 + N) of a run of N + 8 cells.
-template <int N>
-__device__ __forceinline__ void axis_d2_run(const float (&in)[N + 8], float (&out)[N])
-{
-    float d1[N + 1], d2[N + 2];
-#pragma unroll
-    for (int i = 0; i < N + 1; ++i) d1[i] = in[i + 4] - in[i + 3];
-#pragma unroll
-    for (int i = 0; i < N + 2; ++i) d2[i] = in[i + 4] - in[i + 2];
-#pragma unroll
-    for (int i = 0; i < N; ++i)
-        out[i] = axis_d2_shared(in[i] + in[i + 8], in[i + 1] + in[i + 7], d2[i + 2] - d2[i],
-                                d1[i + 1] - d1[i], in[i + 4]);
-}
-
 // 16 bytes per lane from global memory straight into LDS: lane l of the wave
 // writes at lds + 16 l (lds is the wave's address, the same in every lane).
 __device__ __forceinline__ void load_to_lds16(const float *g, float *lds)
