@@ -73,7 +73,7 @@ double single_us(double cells) { return 3.2 + cells * 2.35e-6; }
 // pairs: launches come in pairs that start and end on the same buffers, so a
 // run is cut into whole pairs of `steps` and a rest of one pair (or of one or
 // two single steps).  Otherwise launches follow one another freely.
-MultiPlan plan_multi(const fdk::MultiGrid *grids, int count, int64_t run, bool pairs)
+MultiPlan plan_multi(const fdk::MultiGrid *grids, int count, int64_t run, int mode, bool pairs)
 {
     double cells = 0.0;
     for (int i = 0; i < count; ++i) cells += (double)grids[i].nz * grids[i].px;
@@ -81,7 +81,7 @@ MultiPlan plan_multi(const fdk::MultiGrid *grids, int count, int64_t run, bool p
     double best_us = pairs ? (double)run * single_us(cells) : 1e300;
     double us[fdk::kMultiSteps + 1] = {0.0};
     for (int k = 1; k <= fdk::kMultiSteps; ++k)
-        if (fdk::multi2d_shape(grids, count, k, &us[k]) < 0) us[k] = 1e300;
+        if (fdk::multi2d_shape(grids, count, k, mode, &us[k]) < 0) us[k] = 1e300;
     for (int k = 1; k <= fdk::kMultiSteps && k <= run; ++k) {
         double t;
         if (pairs) {
@@ -146,11 +146,16 @@ fd_status keep_levels(const Flight &f, hipStream_t s)
     return e == hipSuccess ? FD_OK : hip_fail(e, "checkpoint copy");
 }
 
+// Cells that several launches in a row work on together: two pairs of levels
+// and c, 20 bytes a cell, stay in the 256 MB Infinity Cache (12 shots of
+// 2.1 M cells in one launch read everything from HBM each time).
+constexpr double kGroupCells = 9.0e6;
+
 // Steps every flight to its end.  Launches of several steps come in pairs:
 // the first writes the state's second pair of levels, the next one writes
 // back, so that after a pair (and so after every call) level n is in
 // buf[n & 1] again, as single steps leave it.  Same bits either way.
-fd_status advance(Flight *f, int count, hipStream_t s)
+fd_status advance_group(Flight *f, int count, hipStream_t s)
 {
     int64_t run = 0;
     bool paired = true;
@@ -160,7 +165,7 @@ fd_status advance(Flight *f, int count, hipStream_t s)
         paired = paired && f[i].st->pair[0] != nullptr;
         grids[i] = fdk::MultiGrid{(int)f[i].m->L.nz, f[i].m->L.px};
     }
-    const int steps = paired && run > 2 ? plan_multi(grids, count, run, true).steps : 0;
+    const int steps = paired && run > 2 ? plan_multi(grids, count, run, fdk::kFwd, true).steps : 0;
     while (run > 0) {
         if (steps > 0 && run > 2) {
             for (int half = 0; half < 2; ++half) {
@@ -237,6 +242,25 @@ fd_status advance(Flight *f, int count, hipStream_t s)
                 if (f[i].n < f[i].end) f[i].st->next = ++f[i].n;
             run -= 1;
         }
+    }
+    return FD_OK;
+}
+
+// advance_group on consecutive flights of about equal shares, each within
+// kGroupCells where there are enough of them.
+fd_status advance(Flight *f, int count, hipStream_t s)
+{
+    auto cells = [&](int i) { return (double)f[i].m->L.npad; };
+    double total = 0.0;
+    for (int i = 0; i < count; ++i) total += cells(i);
+    const double share = total / std::max(1.0, std::ceil(total / kGroupCells));
+    for (int i = 0; i < count;) {
+        int k = i;
+        double sum = cells(k++);
+        while (k < count && sum + 0.5 * cells(k) <= share) sum += cells(k++);
+        const fd_status st = advance_group(f + i, k - i, s);
+        if (st != FD_OK) return st;
+        i = k;
     }
     return FD_OK;
 }
@@ -401,7 +425,7 @@ fd_status fd_create_model(const fd_grid *grid, const float *velocity, void *mode
         StepArgs a = base_args(m, nullptr, nullptr);
         fdk::plan_tiles(a, L.ndim, L.storage, fdk::kFwd);
         const fdk::MultiGrid mg{(int)L.nz, L.px};
-        if (L.ndim == 2) (void)fdk::multi2d_shape(&mg, 1, 1, nullptr);   // the CU count
+        if (L.ndim == 2) (void)fdk::multi2d_shape(&mg, 1, 1, fdk::kFwd, nullptr);   // the CU count
         (void)hipGetLastError();
     }
     *out = m;
@@ -634,7 +658,7 @@ std::vector<int> cut_steps(int64_t m, int cap, bool even)
     return out;
 }
 
-// backward_pass on 2D grids: several steps per launch.  Two pairs of levels,
+// backward_pass on 2D grids, up to FD_BATCH_MAX shots: several steps per launch.  Two pairs of levels,
 // the recompute state's and the adjoint state's places in the work buffers,
 // serve the adjoint recursion in turn; while a segment is recomputed, the one
 // that does not hold the adjoint state serves the recompute, which reads the
@@ -653,21 +677,17 @@ fd_status backward_2d(const fd_model *model, const ShotIO *io, int32_t count, in
     };
     auto hist = [&](int32_t i, int64_t slot) -> float * { return (float *)io[i].work + (2 + slot) * fl; };
     const int64_t nt = io[0].shot->nt, nseg = n_ckpt(nt, every);
-    const int32_t group = std::min<int32_t>(count, FD_BATCH_MAX);
+    const int32_t group = count;   // at most FD_BATCH_MAX
     std::vector<fdk::MultiGrid> grids((size_t)group, fdk::MultiGrid{(int)L.nz, L.px});
+    // (the recompute's at least 2, so that its last launch writes both fields
+    // of the tail)
+    auto most = [&](int64_t run, int mode) { return std::max(1, plan_multi(grids.data(), group, run, mode, false).steps); };
     const int64_t seg0 = std::min<int64_t>(nt, every);
-    // (at least 2, so that the recompute's last launch writes both fields of
-    // the tail)
-    const int cap = std::max(2, plan_multi(grids.data(), group, seg0, false).steps);
+    const int cap = std::max(2, most(seg0, image ? fdk::kFwdKeep : fdk::kFwdLap)), cap_adj = most(seg0, fdk::kAdj);
     auto launch = [&](auto make_args, int mode) -> hipError_t {
-        for (int32_t i0 = 0; i0 < count; i0 += FD_BATCH_MAX) {
-            fdk::MultiArgs it[FD_BATCH_MAX];
-            int k = 0;
-            for (int32_t i = i0; i < std::min<int32_t>(count, i0 + FD_BATCH_MAX); ++i) it[k++] = make_args(i);
-            const hipError_t e = fdk::launch_multi2d(it, k, mode, s);
-            if (e != hipSuccess) return e;
-        }
-        return hipSuccess;
+        fdk::MultiArgs it[FD_BATCH_MAX];
+        for (int32_t i = 0; i < count; ++i) it[i] = make_args(i);
+        return fdk::launch_multi2d(it, count, mode, s);
     };
     int zp = 1;   // the pair that holds the adjoint state: (z^(k+1), z^(k+2))
     for (int64_t seg = nseg - 1; seg >= 0; --seg) {
@@ -723,7 +743,7 @@ fd_status backward_2d(const fd_model *model, const ShotIO *io, int32_t count, in
             }
         }
         int64_t k = n1;   // adjoint steps k = n1 .. n0+1
-        for (const int c : cut_steps(m, cap, false)) {
+        for (const int c : cut_steps(m, cap_adj, false)) {
             const hipError_t e = launch(
                 [&](int32_t i) {
                     fdk::MultiArgs a = multi_args(model, io[i].shot, 0, c);
@@ -797,7 +817,17 @@ fd_status backward_pass(const fd_model *model, const ShotIO *io, int32_t count, 
         if (e != hipSuccess) return hip_fail(e, "adjoint clear");
         acc[i] = gsum(i);
     }
-    if (L.ndim == 2) return backward_2d(model, io, count, ckpt_every, image, s);
+    if (L.ndim == 2) {
+        // in groups whose fields stay in the Infinity Cache
+        const int32_t most = (int32_t)std::clamp(kGroupCells / (double)L.npad, 1.0, (double)FD_BATCH_MAX);
+        const int32_t groups = (count + most - 1) / most;
+        for (int32_t g = 0; g < groups; ++g) {
+            const int32_t i0 = (int32_t)((int64_t)count * g / groups), i1 = (int32_t)((int64_t)count * (g + 1) / groups);
+            const fd_status st = backward_2d(model, io + i0, i1 - i0, ckpt_every, image, s);
+            if (st != FD_OK) return st;
+        }
+        return FD_OK;
+    }
     auto ckpt_slot = [&](int32_t i, int64_t seg) -> char * {
         return (char *)io[i].ckpt + (size_t)seg * ckpt_slot_bytes(L);
     };

@@ -43,7 +43,7 @@ hipError_t launch_multi2d(const MultiArgs *items, int count, int mode, hipStream
 struct MultiGrid {
     int nz, px;
 };
-int multi2d_shape(const MultiGrid *grids, int count, int steps, double *us);
+int multi2d_shape(const MultiGrid *grids, int count, int steps, int mode, double *us);
 // The step as separate routine kernels (derivative fields dzz, dxx and, in
 // 3D, dyy materialised in HBM); FP32 fields only.
 hipError_t launch_routines(const StepArgs &a, int ndim, float *dzz, float *dxx, float *dyy,

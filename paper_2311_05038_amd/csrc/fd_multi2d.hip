@@ -384,16 +384,28 @@ __global__ __launch_bounds__(TXL *NZ, WPS) void k_multi2d(const MultiBatch<N> b)
 // --------------------------------------------------------------------------
 namespace {
 
-// The tile shapes, with what a launch of them costs (fitted to measurements
-// of 1 to 8 steps on 256^2 to 3001 x 4777): a tile's loads and stores and one
-// step on it, in us.
+// The tile shapes, with what a launch of them costs in us (least squares over
+// 1 to 10 steps on 15 grids and surveys of 200 x 170 to 12 x 700 x 1500; 7% rms):
+// per round of blocks and tile `tile` + `step` for every step, in proportion
+// to the rows that still take part, + `odd` from the second round on when an
+// odd number of steps leaves no buffer to copy the next tile into.  Rows:
+// kFwd; kFwdLap and kFwdKeep; kAdj.
+struct Cost {
+    double tile, step, odd;
+};
 struct Shape {
     int ex, ez;        // ext tile
-    double tile, step;
+    int slack;         // rows a wave covers: it takes part while one is valid
+    Cost cost[3];
 };
-constexpr int kShapes = 3;
-constexpr Shape kShape[kShapes] = {{64, 64, 1.0, 0.95}, {96, 96, 3.0, 1.55}, {128, 128, 4.5, 2.75}};
-constexpr double kLaunchUs = 2.6;
+constexpr int kShapes = 4;
+constexpr Shape kShape[kShapes] = {
+    {64, 64, 4, {{1.55, 0.93, 0.5}, {1.95, 1.16, 0.3}, {3.1, 1.24, 0.5}}},
+    {96, 96, 8, {{3.4, 1.79, 0.7}, {4.6, 1.98, 1.5}, {8.7, 2.31, 1.8}}},
+    {128, 96, 6, {{4.3, 1.91, 1.0}, {6.2, 2.29, 2.2}, {11.8, 2.44, 4.3}}},
+    {128, 128, 8, {{6.2, 2.34, 1.8}, {8.8, 2.79, 3.1}, {18.1, 3.17, 7.1}}},
+};
+constexpr double kLaunchUs = 2.5;
 
 int device_cus()
 {
@@ -421,13 +433,14 @@ void launch_shape(const MultiBatch<N> &b, int shape, hipStream_t s)
 {
     // whole eighths of the device (see the walk over the tiles in the kernel)
     const int per = (b.total + 7) / 8, cus8 = device_cus() / 8;
-    auto go = [&](auto kernel, int threads, int per_cu) {
-        hipLaunchKernelGGL(kernel, dim3(8 * std::min(per, per_cu * cus8)), dim3(threads), 0, s, b);
+    auto go = [&](auto kernel, int threads) {
+        hipLaunchKernelGGL(kernel, dim3(8 * std::min(per, cus8)), dim3(threads), 0, s, b);
     };
     switch (shape) {
-    case 0: go(k_multi2d<16, 1, 64, MODE, 4, N>, 1024, 1); break;
-    case 1: go(k_multi2d<24, 3, 32, MODE, 3, N>, 768, 1); break;
-    default: go(k_multi2d<32, 4, 32, MODE, 4, N>, 1024, 1); break;
+    case 0: go(k_multi2d<16, 1, 64, MODE, 4, N>, 1024); break;
+    case 1: go(k_multi2d<24, 3, 32, MODE, 3, N>, 768); break;
+    case 2: go(k_multi2d<32, 3, 32, MODE, 4, N>, 1024); break;
+    default: go(k_multi2d<32, 4, 32, MODE, 4, N>, 1024); break;
     }
 }
 
@@ -457,17 +470,20 @@ hipError_t launch_items(const MultiArgs *items, int count, int mode, int shape, 
 
 }  // namespace
 
-int multi2d_shape(const MultiGrid *grids, int count, int steps, double *us)
+int multi2d_shape(const MultiGrid *grids, int count, int steps, int mode, double *us)
 {
     int best = -1;
     double best_us = 0.0;
     for (int k = 0; k < kShapes; ++k) {
         const Shape &sh = kShape[k];
-        if (sh.ez - 8 * steps < 16) continue;   // an inner tile of at least 16 x 16
+        const Cost &c = sh.cost[mode == kAdj ? 2 : mode == kFwd ? 0 : 1];
+        if (sh.ez - 8 * steps < 16) continue;   // an inner tile of at least 16 rows
         int64_t tiles = 0;
         for (int i = 0; i < count; ++i) tiles += tiles_of(sh, grids[i].nz, grids[i].px, steps, nullptr);
-        const int64_t rounds = (tiles + device_cus() - 1) / device_cus();
-        const double t = kLaunchUs + (double)rounds * (sh.tile + steps * sh.step);
+        const int64_t blocks = device_cus() / 8 * 8, rounds = (tiles + blocks - 1) / blocks;
+        double t = c.tile + ((steps & 1) && rounds > 1 ? c.odd : 0.0);
+        for (int s = 1; s <= steps; ++s) t += c.step * std::min(1.0, (double)(sh.ez - 8 * s + sh.slack) / sh.ez);
+        t = kLaunchUs + (double)rounds * t;
         if (best < 0 || t < best_us) {
             best = k;
             best_us = t;
@@ -486,7 +502,7 @@ hipError_t launch_multi2d(const MultiArgs *items, int count, int mode, hipStream
         g[i] = MultiGrid{items[i].nz, items[i].px};
         steps = std::max(steps, items[i].steps);
     }
-    const int shape = multi2d_shape(g, count, steps, nullptr);
+    const int shape = multi2d_shape(g, count, steps, mode, nullptr);
     if (shape < 0) return hipErrorInvalidValue;
     return count == 1 ? launch_items<1>(items, count, mode, shape, s)
                       : launch_items<kBatchMax>(items, count, mode, shape, s);
