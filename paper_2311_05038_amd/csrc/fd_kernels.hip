@@ -782,7 +782,7 @@ __global__ __launch_bounds__(64 * NW) void k_step3d(StepArgs a)
 }
 
 // --------------------------------------------------------------------------
-// 3D, FP32, grids too small to fill the device with long chunks
+// 3D, grids too small to fill the device with long chunks
 // --------------------------------------------------------------------------
 constexpr int kShortTX = 64, kShortTY = 16;   // 16 lanes of 4 cells x 16 rows
 
@@ -800,57 +800,69 @@ constexpr int kShortTX = 64, kShortTY = 16;   // 16 lanes of 4 cells x 16 rows
 // adjoint 96 x 120 x 152 14.6 / 12.7, 201 x 333 x 289 108 / 92.  Arithmetic and
 // results are those of k_step3d.  NTS: Pold, c and the new level bypass the
 // caches (grids beyond the Infinity Cache).
-template <int ZC, int MODE, bool NTS>
+template <int ST, int ZC, int MODE, bool CQ, bool NTS>
 __global__ __launch_bounds__(256) void k_step3d_short(StepArgs a)
 {
+    static_assert(ST == kF32 ? !CQ : MODE == kFwd, "16-bit fields: forward steps; 16-bit c with them only");
+    using T = typename Stor<ST>::T;
+    using CT = std::conditional_t<CQ, uint16_t, float>;
+    using PT = Pack<T, 4>;
+    using PC = Pack<CT, 4>;
     constexpr int TX = kShortTX, TY = kShortTY, LW = TX + 8, LH = TY + 8, NT = 16 * TY;
-    // 16-byte loads of the y halo (8 rows a plane) and of the x halo (2 a row)
+    // 4-cell loads of the y halo (8 rows a plane) and of the x halo (2 a row)
     constexpr int YT = 8 * ZC * 16, XT = TY * ZC * 2;
     constexpr int YH = (YT + NT - 1) / NT, XH = (XT + NT - 1) / NT;
     __shared__ __attribute__((aligned(16))) float pl[ZC][LH * LW];
+    __shared__ float red[4];
     const int lx = threadIdx.x & 15, ly = threadIdx.x >> 4;
     const int t = xcd_tile(blockIdx.x, a.tiles_x * a.tiles_y * a.tiles_z);
     const int tx = t % a.tiles_x, t2 = t / a.tiles_x, tz = t2 % a.tiles_z, ty = t2 / a.tiles_z;
     const int xb = tx * TX, yb = ty * TY, zb = tz * ZC, x0 = xb + 4 * lx, y = yb + ly;
-    const int nx = a.nx, ny = a.ny, nz = a.nz, zlo = -a.zghost, zhi = nz + a.zghost;
+    const int nx = a.nx, ny = a.ny, nz = a.nz;
+    const int zlo = ST == kF32 ? -a.zghost : 0, zhi = ST == kF32 ? nz + a.zghost : nz;
     const size_t px = (size_t)a.px, pp = (size_t)ny * px;
     const bool in = x0 < a.px && y < ny;
-    const float *cur = (const float *)a.cur, *prv = (const float *)a.prev;
-    using P4 = Pack<float, 4>;
-    auto load = [&](const float *f, int z, int yy, int xx, bool ok) -> P4 {
-        P4 p{};
-        if (ok) p = ldp<float, 4>(f + (ptrdiff_t)z * (ptrdiff_t)pp + (size_t)yy * px + xx);
+    const T *cur = (const T *)a.cur, *prv = (const T *)a.prev;
+    const CT *cb;
+    if constexpr (CQ)
+        cb = a.c16;
+    else
+        cb = a.c;
+    auto load = [&](int z, int yy, int xx, bool ok) -> PT {
+        PT p{};
+        if (ok) p = ldp<T, 4>(cur + (ptrdiff_t)z * (ptrdiff_t)pp + (size_t)yy * px + xx);
         return p;
     };
-    P4 q[ZC + 8], pv[ZC], cv[ZC], yh[YH], xh[XH];
+    PT q[ZC + 8], pv[ZC], yh[YH], xh[XH];
+    PC cv[ZC];
     int ys[YH], xs[XH];
 #pragma unroll
     for (int k = 0; k < ZC + 8; ++k) {
         const int z = zb - 4 + k;
-        q[k] = load(cur, z, y, x0, in && z >= zlo && z < zhi);
+        q[k] = load(z, y, x0, in && z >= zlo && z < zhi);
     }
 #pragma unroll
     for (int k = 0; k < YH; ++k) {
         const int u = k * NT + (int)threadIdx.x, zz = u / 128, r = (u >> 4) & 7, xx = xb + 4 * (u & 15);
         const int row = r < 4 ? r : TY + r, yy = yb + row - 4;   // row of the LDS plane
-        yh[k] = load(cur, zb + zz, yy, xx, u < YT && xx < a.px && yy >= 0 && yy < ny && zb + zz < nz);
+        yh[k] = load(zb + zz, yy, xx, u < YT && xx < a.px && yy >= 0 && yy < ny && zb + zz < nz);
         ys[k] = u < YT ? zz * LH * LW + row * LW + 4 + 4 * (u & 15) : -1;
     }
 #pragma unroll
     for (int k = 0; k < XH; ++k) {
         const int u = k * NT + (int)threadIdx.x, zz = u / (2 * TY), r = (u >> 1) % TY, side = u & 1;
         const int xx = side ? xb + TX : xb - 4, yy = yb + r;
-        xh[k] = load(cur, zb + zz, yy, xx, u < XT && xx >= 0 && xx < a.px && yy < ny && zb + zz < nz);
+        xh[k] = load(zb + zz, yy, xx, u < XT && xx >= 0 && xx < a.px && yy < ny && zb + zz < nz);
         xs[k] = u < XT ? zz * LH * LW + (r + 4) * LW + (side ? 4 + TX : 0) : -1;
     }
 #pragma unroll
     for (int k = 0; k < ZC; ++k) {
-        pv[k] = P4{};
-        cv[k] = P4{};
+        pv[k] = PT{};
+        cv[k] = PC{};
         if (in && zb + k < nz) {
             const size_t e = (size_t)(zb + k) * pp + (size_t)y * px + x0;
-            pv[k] = NTS ? ldp_stream<float, 4>(prv + e) : ldp<float, 4>(prv + e);
-            cv[k] = NTS ? ldp_stream<float, 4>(a.c + e) : ldp<float, 4>(a.c + e);
+            pv[k] = NTS ? ldp_stream<T, 4>(prv + e) : ldp<T, 4>(prv + e);
+            cv[k] = NTS ? ldp_stream<CT, 4>(cb + e) : ldp<CT, 4>(cb + e);
         }
     }
     float gx[4];
@@ -863,69 +875,102 @@ __global__ __launch_bounds__(256) void k_step3d_short(StepArgs a)
     float inj = 0.0f;
     if constexpr (MODE != kAdj)
         if (a.n + 1 < a.nt) inj = a.amp * a.wavelet[a.n + 1];
+    const HalfCtx h = half_prologue<ST>(a, inj, blockIdx.x == 0);
 
     float *base = &pl[0][0];
+    auto put = [&](float *at_l, const PT &p) {
+        Pack<float, 4> o;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) o.v[v] = decode_raw<ST>(p.v[v]);
+        stp<float, 4>(at_l, o);
+    };
     const int li = (ly + 4) * LW + 4 + 4 * lx;
 #pragma unroll
-    for (int k = 0; k < ZC; ++k) stp<float, 4>(pl[k] + li, q[k + 4]);
+    for (int k = 0; k < ZC; ++k) put(pl[k] + li, q[k + 4]);
 #pragma unroll
     for (int k = 0; k < YH; ++k)
-        if (ys[k] >= 0) stp<float, 4>(base + ys[k], yh[k]);
+        if (ys[k] >= 0) put(base + ys[k], yh[k]);
 #pragma unroll
     for (int k = 0; k < XH; ++k)
-        if (xs[k] >= 0) stp<float, 4>(base + xs[k], xh[k]);
+        if (xs[k] >= 0) put(base + xs[k], xh[k]);
     __syncthreads();
 
     float lz[ZC][4];
+    if constexpr (ST == kF32) {
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-        float col[ZC + 8], out[ZC];
+        for (int v = 0; v < 4; ++v) {
+            float col[ZC + 8], out[ZC];
 #pragma unroll
-        for (int k = 0; k < ZC + 8; ++k) col[k] = q[k].v[v];
-        axis_d2_run<ZC>(col, out);
+            for (int k = 0; k < ZC + 8; ++k) col[k] = q[k].v[v];
+            axis_d2_run<ZC>(col, out);
 #pragma unroll
-        for (int k = 0; k < ZC; ++k) lz[k][v] = out[k];
+            for (int k = 0; k < ZC; ++k) lz[k][v] = out[k];
+        }
     }
-    const HalfCtx h{1.0f, 1.0f, 1.0f, 1.0f};
     float bmax = 0.0f;
 #pragma unroll
     for (int k = 0; k < ZC; ++k) {
         const int z = zb + k;
         if (z >= nz) break;
         const float *P = pl[k] + li;
-        const P4 xl = ldp<float, 4>(P - 4), xr = ldp<float, 4>(P + 4);
-        P4 r[8];
+        const Pack<float, 4> xl = ldp<float, 4>(P - 4), xr = ldp<float, 4>(P + 4);
+        Pack<float, 4> r[8];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             r[e] = ldp<float, 4>(P + (e - 4) * LW);
             r[4 + e] = ldp<float, 4>(P + (e + 1) * LW);
         }
-        float row[12], lxx[4];
+        float row[12];
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             row[v] = xl.v[v];
-            row[4 + v] = q[k + 4].v[v];
+            row[4 + v] = decode_raw<ST>(q[k + 4].v[v]);
             row[8 + v] = xr.v[v];
         }
-        axis_d2_run<4>(row, lxx);
         float nw[4], lp[4], G[4], pc[4], cc[4];
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            const float u = q[k + 4].v[v];
-            const float lyy = axis_d2(r[0].v[v], r[1].v[v], r[2].v[v], r[3].v[v], u, r[4].v[v], r[5].v[v],
-                                      r[6].v[v], r[7].v[v]);
-            const float lap = lz[k][v] + (lyy + lxx[v]);
-            pc[v] = pv[k].v[v];
-            cc[v] = cv[k].v[v];
-            G[v] = (gz[k] * gy) * gx[v];
-            nw[v] = leapfrog(G[v], u, cc[v], lap, pc[v]);
-            lp[v] = MODE == kAdj ? u : lap;
+            pc[v] = decode_raw<ST>(pv[k].v[v]);
+            cc[v] = (float)cv[k].v[v];
         }
-        Outgoing<float, 4> out;
-        finish_cells<kF32, 4, MODE, NTS, false>(a, h, z, y, x0, in, (size_t)z * pp + (size_t)y * px, (uint32_t)x0,
-                                                  nw, lp, pc, cc, G, inj, bmax, out);
-        flush<float, 4, MODE, NTS>(out);
+        if constexpr (ST == kF32) {
+            float lxx[4];
+            axis_d2_run<4>(row, lxx);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const float u = row[4 + v];
+                const float lyy = axis_d2(r[0].v[v], r[1].v[v], r[2].v[v], r[3].v[v], u, r[4].v[v], r[5].v[v],
+                                          r[6].v[v], r[7].v[v]);
+                const float lap = lz[k][v] + (lyy + lxx[v]);
+                G[v] = (gz[k] * gy) * gx[v];
+                nw[v] = leapfrog(G[v], u, cc[v], lap, pc[v]);
+                lp[v] = MODE == kAdj ? u : lap;
+            }
+        } else {
+            // the operations of the streaming kernel's 16-bit step, in its order
+            const float gr = gz[k] * gy;
+            const float sc = CQ ? h.sc * a.c16_scale : h.sc, two = CQ ? 2.0f * a.c16_inv : 2.0f;
+            const float r1 = gr * sc, r2 = (gr * gr) * h.sp;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                float sk[4];
+#pragma unroll
+                for (int e = 1; e <= 4; ++e)
+                    sk[e - 1] = ((row[4 + v - e] + row[4 + v + e]) + (r[4 - e].v[v] + r[3 + e].v[v])) +
+                                (decode_raw<ST>(q[k + 4 - e].v[v]) + decode_raw<ST>(q[k + 4 + e].v[v]));
+                const float ctr = row[4 + v];
+                const float lap = fmaf(3.0f * kA0, ctr, fmaf(kA4, sk[3], fmaf(kA3, sk[2], fmaf(kA2, sk[1], kA1 * sk[0]))));
+                G[v] = 0.0f;
+                nw[v] = fmaf(gx[v] * r1, fmaf(cc[v], lap, two * ctr), -((gx[v] * gx[v]) * r2) * pc[v]);
+                lp[v] = lap;
+            }
+        }
+        Outgoing<T, 4> out;
+        finish_cells<ST, 4, MODE, NTS, false>(a, h, z, y, x0, in, (size_t)z * pp + (size_t)y * px, (uint32_t)x0,
+                                              nw, lp, pc, cc, G, inj, bmax, out);
+        flush<T, 4, MODE, NTS>(out);
     }
+    if constexpr (ST != kF32) block_max_to<NT>(max_slot(a.meta, (int)((a.n + 1) & 3)), bmax * h.sn, red);
 }
 
 // --------------------------------------------------------------------------
@@ -1406,6 +1451,14 @@ void plan_tiles(StepArgs &a, int ndim, int storage, int mode)
                 return;
             }
         }
+        if (storage != kF32 && (int64_t)a.px * a.ny * a.nz <= 3000000) {
+            a.vx = 1;
+            a.zc = (int64_t)a.px * a.ny * a.nz <= 1000000 ? 2 : 4;
+            a.tiles_x = (a.px + kShortTX - 1) / kShortTX;
+            a.tiles_y = (a.ny + kShortTY - 1) / kShortTY;
+            a.tiles_z = (a.nz + a.zc - 1) / a.zc;
+            return;
+        }
         const int VX = storage == kF32 ? k3dVX32 : k3dVX16;
         const int RY = storage == kF32 ? (narrow ? k3dRYN32 : k3dRY32) : k3dRY16;
         const int NW = storage == kF32 ? FD_3D_NW32 : FD_3D_NW16;
@@ -1447,11 +1500,11 @@ static void launch3d(const StepArgs &a, int nb, hipStream_t s)
 {
     if constexpr (ST == kF32) {
         if (a.vx == 1 && a.zc == 2)
-            hipLaunchKernelGGL((k_step3d_short<2, MODE, false>), dim3(nb), dim3(256), 0, s, a);
+            hipLaunchKernelGGL((k_step3d_short<kF32, 2, MODE, false, false>), dim3(nb), dim3(256), 0, s, a);
         else if (a.vx == 1)
-            hipLaunchKernelGGL((k_step3d_short<4, MODE, false>), dim3(nb), dim3(256), 0, s, a);
+            hipLaunchKernelGGL((k_step3d_short<kF32, 4, MODE, false, false>), dim3(nb), dim3(256), 0, s, a);
         else if (a.vx == 0 || MODE == kAdj)   // (the plan gives the adjoint no other)
-            hipLaunchKernelGGL((k_step3d_short<4, MODE, true>), dim3(nb), dim3(256), 0, s, a);
+            hipLaunchKernelGGL((k_step3d_short<kF32, 4, MODE, false, true>), dim3(nb), dim3(256), 0, s, a);
         else if constexpr (MODE != kAdj) {
             if (a.vx * 64 == k3dTXN32)
                 hipLaunchKernelGGL((k_step3d<ST, k3dVX32, k3dRYN32, FD_3D_NW32, k3dRPWN32, MODE, false>), dim3(nb),
@@ -1461,6 +1514,10 @@ static void launch3d(const StepArgs &a, int nb, hipStream_t s)
                                    dim3(64 * FD_3D_NW32), 0, s, a);
         }
     }
+    else if (a.vx == 1 && a.zc == 2)
+        hipLaunchKernelGGL((k_step3d_short<ST, 2, MODE, CQ, false>), dim3(nb), dim3(256), 0, s, a);
+    else if (a.vx == 1)
+        hipLaunchKernelGGL((k_step3d_short<ST, 4, MODE, CQ, false>), dim3(nb), dim3(256), 0, s, a);
     else
         hipLaunchKernelGGL((k_step3d<ST, k3dVX16, k3dRY16, FD_3D_NW16, FD_3D_RPW16, MODE, CQ>), dim3(nb),
                            dim3(64 * FD_3D_NW16), 0, s, a);

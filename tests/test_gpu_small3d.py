@@ -99,3 +99,22 @@ def test_16bit_2d_tiles_agree(storage, c_storage, nz, nx):
         out.append((tr, state.wavefield(0)[:40, 90:211].clone()))
     assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
     assert float(out[0][1].abs().max()) > 0
+
+
+@pytest.mark.parametrize("storage,c_storage", [(1, 0), (2, 0), (1, 1), (2, 1)])
+@pytest.mark.parametrize("nz,ny,nx", [(39, 60, 63), (40, 81, 130), (41, 150, 200)])
+def test_16bit_3d_tiles_agree(storage, c_storage, nz, ny, nx):
+    """The same in 3D: 2 and 4 planes per block against the streaming kernel
+    on the padded grid (8 steps reach 32 cells)."""
+    import torch
+    from helpers import setup
+    p = _problem(3, nz, ny, nx, 8, seed=6).scaled(src=(3, 25, 30), sponge_width=0, velocity_kind="constant",
+                                                  receivers=fi.Receivers(2, 10, 5, 1, 30, 50))
+    q = p.scaled(nz=120, ny=200, nx=260)
+    out = []
+    for r in (p, q):
+        model, state, shot = setup(r, storage=storage, c_storage=c_storage)
+        tr = model.run_shot(state, shot)
+        out.append((tr, state.wavefield(0)[:35, :57, :62].clone()))
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+    assert float(out[0][1].abs().max()) > 0
