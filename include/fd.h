@@ -222,10 +222,11 @@ fd_status fd_run_shot(const fd_model *model, fd_state *state, const fd_shot *sho
 /* A recorded shot: the launches of fd_run_shot (without checkpoints) for
  * one (model, state, shot, traces) captured once into a HIP graph, so that
  * a shot on a grid too small to fill the GPU pays one graph launch instead
- * of one kernel launch per step.  Section 7's roofline places the step at
- * the memory bound; on small grids (e.g. 256^2) a step streams its bytes in
- * less time than a kernel launch takes, and the launches, not the memory,
- * set the pace.  Opaque handle. */
+ * of its kernel launches (one for several steps in 2D FP32, otherwise one
+ * per step).  Section 7's roofline places the step at the memory bound; on
+ * small grids (e.g. 256^2) a step streams its bytes in less time than a
+ * kernel launch takes, and the launches, not the memory, set the pace.
+ * Opaque handle. */
 typedef struct fd_shot_graph fd_shot_graph;
 
 /* Records fd_begin_shot and steps 0..nt-1 of `shot` on (model, state), with
@@ -379,9 +380,10 @@ typedef struct {
 } fd_batch_item;
 
 /* Advances every item by up to `nsteps` steps with kernel launches that
- * each cover all items, one or several steps at a time (continuous batching
- * of shots on grids of different sizes).  An item stops at its last step; items[i].n is updated
- * (host) to the next step of each item.  Results equal fd_step on each
+ * each cover all items or a group of them, one or several steps at a time
+ * (continuous batching of shots on grids of different sizes).  An item stops
+ * at its last step; items[i].n is updated (host) to the next step of each
+ * item.  Results equal fd_step on each
  * item alone, bit for bit.  2D, FP32 storage, count <= FD_BATCH_MAX. */
 fd_status fd_step_batch(fd_batch_item *items, int32_t count, int32_t nsteps, void *stream);
 

@@ -391,9 +391,10 @@ class State:
 class ShotGraph:
     """fd_shot_graph_create: the launches of Model.run_shot(state, shot,
     traces) recorded once into a HIP graph; launch() replays them (one graph
-    launch instead of one kernel launch per step).  The graph keeps the
-    addresses of the model, state, wavelet and traces, which this object
-    keeps alive; replays read their contents as they are then."""
+    launch instead of one kernel launch per step, or per few steps in 2D
+    FP32).  The graph keeps the addresses of the model, state, wavelet and
+    traces, which this object keeps alive; replays read their contents as
+    they are then."""
 
     def __init__(self, model: "Model", state: "State", shot: Shot,
                  traces: Optional[torch.Tensor] = None):

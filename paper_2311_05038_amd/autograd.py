@@ -20,8 +20,8 @@ from . import Grid, Model, Shot, _alloc
 
 # Shots are independent: a call processes them in groups of up to
 # GROUP shots with the library's multi-shot entry points (fd_run_shots,
-# fd_adjoint_gradient_shots, fd_rtm_image_shots), which in 2D advance every
-# shot of a group with one kernel launch per time step.  Each shot of a
+# fd_adjoint_gradient_shots, fd_rtm_image_shots), which in 2D advance the
+# shots together, several time steps per kernel launch.  Each shot of a
 # group holds its own state, checkpoints and work buffer.
 GROUP = 16
 

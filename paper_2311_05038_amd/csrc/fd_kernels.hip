@@ -10,7 +10,9 @@
 //   (256x8 cells for FP32 fields, 128x8 for 16-bit) and a chunk of `zc`
 //   planes; lanes stream along z (the slow axis) with a 9-deep register queue
 //   per cell, and x/y neighbours come from a double-buffered LDS copy of the
-//   current plane with a 4-cell halo.
+//   current plane with a 4-cell halo.  Grids whose fields stay in the Infinity
+//   Cache, and the adjoint step, take 2 or 4 planes per block instead, all
+//   loads in flight at once (k_step3d_short).
 // Both follow the fused step of arXiv 2311.05038, Section 7 (Listing 3's
 // add_source, fd_pzz, fd_pxx, fd_time and swap in one pass).
 #include <algorithm>
@@ -1348,10 +1350,9 @@ constexpr int k3dVX16 = FD_3D_VX16, k3dRY16 = FD_3D_RY16;   // 16-bit fields
 // waves per SIMD).  The wide tile is faster on large grids that it fits
 // (512^3 369 against 390 us, 768x768x512 860 against 925: about 5.5% per
 // column), the narrow one where the x size leaves much of the last 256-wide
-// tile empty (384^3 210 -> 155 us, 320x512x512 328 -> 248, 640x640x256 358
-// -> 310, 896x448x256 331 -> 305) and on small grids, which need short
-// z-chunks to fill the device and gain from twice the columns (256^3 55 ->
-// 51 us, 768x256x256 140 -> 135); same bits either way.
+// tile empty (384^3 210 -> 155 us, 640x640x256 358 -> 310, 896x448x256 331 ->
+// 305) and below 2^26 cells, where short z-chunks fill the device and twice
+// the columns help (768x256x256 140 -> 135); same bits either way.
 constexpr int k3dRYN32 = 1, k3dRPWN32 = 2;
 constexpr int k3dTXW32 = 64 / FD_3D_RPW32 * k3dVX32, k3dTXN32 = 64 / k3dRPWN32 * k3dVX32;
 
@@ -1422,7 +1423,11 @@ static int64_t resident_blocks_3d(int storage, bool cq, bool narrow)
 // cells and 4 above (100 x 200 x 300 23.0 / 23.8 us, 201 x 333 x 289 61.5 /
 // 58).  Beyond, with accesses that bypass the caches, it stays ahead for the
 // adjoint step (384^3 239 against 260 us, 512^3 560 against 562) and where
-// the streaming tiles are mostly padding (300^3 87 against 94).
+// the streaming tiles are mostly padding (300^3 87 against 94).  With 16-bit
+// fields it pays up to 3 M padded cells (BF16, streaming / short: 48^3 9.7 /
+// 6.4 us, 66x480x49 16.9 / 10.0, 96x120x152 14.3 / 11.8); the streaming
+// kernel's fewer, longer blocks read the magnitude words and fold a maximum
+// less often, and larger grids keep it.
 void plan_tiles(StepArgs &a, int ndim, int storage, int mode)
 {
     if (ndim == 2) {

@@ -3,8 +3,8 @@
 Requests (one shot each, on its own 2D grid and velocity model) arrive over
 time.  The scheduler admits a waiting request as soon as a batch slot is free
 and its device footprint fits the HBM budget, starts it (model set-up and
-first source addition), and advances every admitted shot with ONE batched
-kernel launch per time step (``fd_step_batch``), so that work of shots that
+first source addition), and advances every admitted shot with batched kernel
+launches of one or several time steps (``fd_step_batch``), so that work of shots that
 arrived at different times overlaps on the device.  A shot leaves the batch
 after its last step; its memory returns to the budget once the device has
 passed that step.  Latency = completion - arrival.
