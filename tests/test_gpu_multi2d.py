@@ -98,6 +98,28 @@ def test_a_batch_whose_shots_end_at_different_steps():
         assert torch.equal(f[1].wavefield(0), ref[1]) and torch.equal(f[1].wavefield(1), ref[2])
 
 
+@pytest.mark.parametrize("grids", [
+    [(2048, 4095), (2047, 4096)],                                   # one group each
+    [(1447, 1449)] * 7,                                             # groups of several
+    [(2048, 4095)] * 2 + [(33, 70)] + [(2047, 4096)] * 2,           # together
+    [(600, 500), (3001, 3002), (40, 50), (1700, 3100), (2, 2)],     # uneven shares
+])
+def test_shots_beyond_the_infinity_cache(grids):
+    import torch
+    import paper_2311_05038_amd as fd
+    flights, refs = [], []
+    for i, (nz, nx) in enumerate(grids):
+        p = _problem(nz, nx, 11 + 2 * (i % 3), seed=80 + i)
+        model, state, shot, levels = _start(p, 30 + i)
+        refs.append(_by_single_steps(model, shot, levels, p))
+        flights.append((model, state, shot, torch.full((shot.nt, shot.nrec), float("nan"), device="cuda")))
+    while any(f[1].next < f[2].nt for f in flights):
+        fd.step_batch(flights, 9)
+    for f, ref in zip(flights, refs):
+        assert torch.equal(f[3], ref[0])
+        assert torch.equal(f[1].wavefield(0), ref[1]) and torch.equal(f[1].wavefield(1), ref[2])
+
+
 def test_a_state_buffer_of_two_levels_is_enough():
     """A buffer without the second pair of levels is accepted, as it was, and
     gives the same bits by single steps; one byte less than that is refused."""
