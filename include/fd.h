@@ -256,8 +256,9 @@ fd_status fd_shot_graph_destroy(fd_shot_graph *graph);
  * dense FP64, +=) the gradient dJ/dv of a scalar J of the traces, given
  * adj = dJ/dtraces (device FP32 [nt][nrec]) and the checkpoints fd_run_shot
  * saved for this model and shot with the same ckpt_every (ckpt_bytes as
- * given to fd_run_shot).  Each checkpoint
- * segment is recomputed, then the adjoint field is stepped backward:
+ * given to fd_run_shot; a copy of them may lie at any address).  Each
+ * checkpoint segment is recomputed, then the adjoint field is stepped
+ * backward:
  *   z^k = G (2 z^{k+1} + c L z^{k+1}) - G^2 z^{k+2} + c G R^T adj[k-1],
  *   dJ/dc += z^k / c * L(P^{k-1}),   dJ/dv = dJ/dc * 2 c / v,
  * with the time sum accumulated in FP64 on the device.

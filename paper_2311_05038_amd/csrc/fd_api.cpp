@@ -676,6 +676,16 @@ std::vector<int> cut_steps(int64_t m, int cap, bool even)
     return out;
 }
 
+const char *ckpt_slot(const Layout &L, const void *ckpt, int64_t seg)
+{
+    return (const char *)ckpt + (size_t)seg * ckpt_slot_bytes(L);
+}
+
+// Whether the step kernels may read levels at `p`: they load 16 bytes at a
+// time (a slot and its levels are multiples of 256 bytes, so the buffer's
+// address decides).
+bool vector_aligned(const void *p) { return (uintptr_t)p % 16 == 0; }
+
 // backward_pass on 2D grids, up to FD_BATCH_MAX shots: several steps per launch.  Two pairs of levels,
 // the recompute state's and the adjoint state's places in the work buffers,
 // serve the adjoint recursion in turn; while a segment is recomputed, the one
@@ -710,12 +720,29 @@ fd_status backward_2d(const fd_model *model, const ShotIO *io, int32_t count, in
     int zp = 1;   // the pair that holds the adjoint state: (z^(k+1), z^(k+2))
     for (int64_t seg = nseg - 1; seg >= 0; --seg) {
         const int64_t n0 = seg * every, n1 = std::min<int64_t>(nt, n0 + every), m = n1 - n0;
-        auto saved = [&](int32_t i, int which) -> const float * {
-            return (const float *)((const char *)io[i].ckpt + (size_t)seg * ckpt_slot_bytes(L) + which * L.field);
+        const std::vector<int> cut = !image ? cut_steps(m, cap, true)
+                                     : m > 1 ? cut_steps(m - 1, cap, false) : std::vector<int>(1, 0);
+        // The kernel reads 16 bytes at a time: a checkpoint at an address that
+        // does not allow it is copied first, to levels that the launch reading
+        // it does not write (the gradient's launch 0 of several writes the
+        // free pair, and not the history's last two fields).
+        auto restored = [&](int32_t i, int which) -> float * {
+            return image || cut.size() == 1 ? level(i, 1 - zp, which) : hist(i, m - 2 + which);
         };
+        auto saved = [&](int32_t i, int which) -> const float * {
+            if (!vector_aligned(io[i].ckpt)) return restored(i, which);
+            return (const float *)(ckpt_slot(L, io[i].ckpt, seg) + which * L.field);
+        };
+        for (int32_t i = 0; i < count; ++i) {
+            if (vector_aligned(io[i].ckpt)) continue;
+            for (int which = 0; which < 2; ++which) {
+                const hipError_t e = hipMemcpyAsync(restored(i, which), ckpt_slot(L, io[i].ckpt, seg) + which * L.field,
+                                                    L.field, hipMemcpyDeviceToDevice, s);
+                if (e != hipSuccess) return hip_fail(e, "checkpoint restore");
+            }
+        }
         if (image) {
             // slot p holds w^(n0+p); slot 0 is the checkpoint's P
-            const std::vector<int> cut = m > 1 ? cut_steps(m - 1, cap, false) : std::vector<int>(1, 0);
             int64_t p = 0;
             for (const int k : cut) {
                 const hipError_t e = launch(
@@ -733,7 +760,6 @@ fd_status backward_2d(const fd_model *model, const ShotIO *io, int32_t count, in
                 p += k;
             }
         } else {
-            const std::vector<int> cut = cut_steps(m, cap, true);
             int64_t p = 0;
             for (size_t l = 0; l < cut.size(); ++l) {
                 const bool last = l + 1 == cut.size();
@@ -846,19 +872,24 @@ fd_status backward_pass(const fd_model *model, const ShotIO *io, int32_t count, 
         }
         return FD_OK;
     }
-    auto ckpt_slot = [&](int32_t i, int64_t seg) -> char * {
-        return (char *)io[i].ckpt + (size_t)seg * ckpt_slot_bytes(L);
-    };
     for (int64_t seg = nseg - 1; seg >= 0; --seg) {
         const int64_t n0 = seg * ckpt_every;
         const int64_t n1 = std::min<int64_t>(nt, n0 + ckpt_every);
         if (image) {
             // The image's history is the field itself: slot s holds w^(n0+s).
             // Slot 0 is the checkpoint's P; each recompute step reads its
-            // Pold from the checkpoint or the slot before and writes the next
-            // level into the next slot (out of place), a plain forward step.
+            // Pold from the checkpoint (or, where its address does not allow
+            // vector loads, a copy in the recompute state's place) or the
+            // slot before and writes the next level into the next slot (out
+            // of place), a plain forward step.
+            auto pold = [&](int32_t i) -> void * {
+                return vector_aligned(io[i].ckpt) ? (void *)(ckpt_slot(L, io[i].ckpt, seg) + L.field) : fw(i, 0);
+            };
             for (int32_t i = 0; i < count; ++i) {
-                hipError_t e = hipMemcpyAsync(hist(i, 0), ckpt_slot(i, seg), L.field, hipMemcpyDeviceToDevice, s);
+                const char *slot = ckpt_slot(L, io[i].ckpt, seg);
+                hipError_t e = hipMemcpyAsync(hist(i, 0), slot, L.field, hipMemcpyDeviceToDevice, s);
+                if (e == hipSuccess && !vector_aligned(io[i].ckpt))
+                    e = hipMemcpyAsync(fw(i, 0), slot + L.field, L.field, hipMemcpyDeviceToDevice, s);
                 if (e != hipSuccess) return hip_fail(e, "checkpoint restore");
             }
             for (int64_t n = n0; n + 1 < n1; ++n) {
@@ -866,7 +897,7 @@ fd_status backward_pass(const fd_model *model, const ShotIO *io, int32_t count, 
                     [&](int32_t i) {
                         StepArgs a = base_args(model, io[i].shot);
                         a.cur = hist(i, n - n0);
-                        a.prev = n == n0 ? (void *)(ckpt_slot(i, seg) + L.field) : (void *)hist(i, n - 1 - n0);
+                        a.prev = n == n0 ? pold(i) : (void *)hist(i, n - 1 - n0);
                         a.out = hist(i, n + 1 - n0);
                         a.n = n;
                         a.trace_row = nullptr;
@@ -877,7 +908,7 @@ fd_status backward_pass(const fd_model *model, const ShotIO *io, int32_t count, 
             }
         } else {
             for (int32_t i = 0; i < count; ++i) {
-                const char *slot = ckpt_slot(i, seg);
+                const char *slot = ckpt_slot(L, io[i].ckpt, seg);
                 hipError_t e = hipMemcpyAsync(fw(i, n0), slot, L.field, hipMemcpyDeviceToDevice, s);
                 if (e == hipSuccess) e = hipMemcpyAsync(fw(i, n0 + 1), slot + L.field, L.field, hipMemcpyDeviceToDevice, s);
                 if (e != hipSuccess) return hip_fail(e, "checkpoint restore");
