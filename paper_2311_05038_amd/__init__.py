@@ -184,8 +184,16 @@ class Model:
     def sizes_for(self, nt: int, ckpt_every: int) -> fd_sizes:
         return _abi.fd_query_bytes(self._g, nt, ckpt_every)
 
-    def new_state(self) -> "State":
-        return State(self)
+    @property
+    def least_state_bytes(self) -> int:
+        """Size of a state buffer without the second pair of levels that
+        sizes.state counts on 2D FP32 grids (a checkpoint is one pair)."""
+        if self.grid.ndim != 2 or self.grid.storage != FD_F32:
+            return self.sizes.state
+        return self.sizes.state - self.sizes_for(1, 1).checkpoints
+
+    def new_state(self, second_pair: bool = True) -> "State":
+        return State(self, second_pair)
 
     def run_shot(self, state: "State", shot: Shot, traces: Optional[torch.Tensor] = None,
                  ckpt: Optional[torch.Tensor] = None, ckpt_every: int = 0,
@@ -303,12 +311,24 @@ class Model:
 
 
 class State:
-    """fd_create_state: the two time levels of one shot in flight."""
+    """fd_create_state: the two time levels of one shot in flight, and on 2D
+    FP32 grids the second pair of levels with which the calls of many steps
+    take several per launch.  second_pair=False leaves that pair out (half the
+    memory, for programs that only call step or keep many states), and so does
+    a device without room for it; every result is the same bits."""
 
-    def __init__(self, model: Model):
+    def __init__(self, model: Model, second_pair: bool = True):
         self.model = model
-        self.buf = _alloc(model.sizes.state, model.device)
-        self.handle = _abi.fd_create_state(model.handle, self.buf.data_ptr(), model.sizes.state)
+        self.buf = None
+        if second_pair:
+            try:
+                self.buf = _alloc(model.sizes.state, model.device)
+            except torch.cuda.OutOfMemoryError:
+                if model.least_state_bytes == model.sizes.state:
+                    raise
+        if self.buf is None:
+            self.buf = _alloc(model.least_state_bytes, model.device)
+        self.handle = _abi.fd_create_state(model.handle, self.buf.data_ptr(), _nbytes(self.buf))
         self.next = -1
 
     @staticmethod

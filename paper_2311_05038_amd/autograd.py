@@ -22,7 +22,9 @@ from . import Grid, Model, Shot, _alloc
 # GROUP shots with the library's multi-shot entry points (fd_run_shots,
 # fd_adjoint_gradient_shots, fd_rtm_image_shots), which in 2D advance the
 # shots together, several time steps per kernel launch.  Each shot of a
-# group holds its own state, checkpoints and work buffer.
+# group holds its own checkpoints and, in turn, its state (made last, so that
+# it can do without its second pair of levels where memory is short, and given
+# back before the backward pass) and its work buffer.
 GROUP = 16
 
 
@@ -49,6 +51,7 @@ class FDTraces(torch.autograd.Function):
             states = [model.new_state() for _ in idx]
             model.run_shots(states, [shots[i] for i in idx], traces[idx[0]:idx[-1] + 1],
                             [ckpts[i] for i in idx], ckpt_every)
+            del states
         ctx.model = model
         ctx.shots = list(shots)
         ctx.ckpts = ckpts
@@ -93,9 +96,11 @@ def l2_misfit_gradient(v: torch.Tensor, grid: Grid, shots: Sequence[Shot],
     need = model.sizes_for(nt, ckpt_every).adjoint_work
     for idx in _groups(len(shots), group):
         sh = [shots[i] for i in idx]
-        states = [model.new_state() for _ in idx]
         ckpts = [model.checkpoint_buffer(nt, ckpt_every) for _ in idx]
-        tr = model.run_shots(states, sh, None, ckpts, ckpt_every)
+        tr = torch.empty((len(idx), nt, sh[0].nrec), dtype=torch.float32, device=v.device)
+        states = [model.new_state() for _ in idx]
+        model.run_shots(states, sh, tr, ckpts, ckpt_every)
+        del states
         res = (tr - observed[idx[0]:idx[-1] + 1]).contiguous()
         J += 0.5 * (res.double() ** 2).sum()
         works = [_alloc(need, model.device) for _ in idx]
@@ -117,9 +122,11 @@ def rtm_image(v: torch.Tensor, grid: Grid, shots: Sequence[Shot], data: torch.Te
     d = data.to(torch.float32).contiguous()
     for idx in _groups(len(shots), group):
         sh = [shots[i] for i in idx]
-        states = [model.new_state() for _ in idx]
         ckpts = [model.checkpoint_buffer(nt, ckpt_every) for _ in idx]
-        model.run_shots(states, sh, None, ckpts, ckpt_every)
+        tr = torch.empty((len(idx), nt, sh[0].nrec), dtype=torch.float32, device=v.device)
+        states = [model.new_state() for _ in idx]
+        model.run_shots(states, sh, tr, ckpts, ckpt_every)
+        del states, tr
         works = [_alloc(need, model.device) for _ in idx]
         model.rtm_image_shots(sh, [d[i] for i in idx], ckpts, ckpt_every, img, works=works)
     return img

@@ -251,7 +251,7 @@ fd_status advance_group(Flight *f, int count, hipStream_t s)
 // tiles.  Together and in groups, ms: 12 mixed shots of 0.3 to 8 M cells
 // 7.94, 8.31; 12 of 1448^2 6.22, 5.80; 2 of 2048 x 4096 4.12, 3.68; 12 of
 // them 11.0, 11.2.
-fd_status advance(Flight *f, int count, hipStream_t s)
+fd_status advance_alike(Flight *f, int count, hipStream_t s)
 {
     fdk::MultiGrid grids[FD_BATCH_MAX];
     double total = 0.0;
@@ -278,6 +278,33 @@ fd_status advance(Flight *f, int count, hipStream_t s)
     if (groups == 0) first[groups = 1] = count;
     for (int g = 0; g < groups; ++g) {
         const fd_status st = advance_group(f + first[g], first[g + 1] - first[g], s);
+        if (st != FD_OK) return st;
+    }
+    return FD_OK;
+}
+
+// Shots with a second pair of levels, then those without: one that has none
+// must not make the others of a call take single steps.  (Where all take
+// single steps, they share the launches.)
+fd_status advance(Flight *f, int count, hipStream_t s)
+{
+    int64_t run = 0;
+    int paired = 0;
+    for (int i = 0; i < count; ++i) {
+        run = std::max(run, f[i].end - f[i].n);
+        paired += f[i].st->pair[0] != nullptr;
+    }
+    if (run <= 2 || paired == 0 || paired == count) return advance_alike(f, count, s);
+    for (const bool with : {true, false}) {
+        Flight g[FD_BATCH_MAX];
+        int at[FD_BATCH_MAX], k = 0;
+        for (int i = 0; i < count; ++i)
+            if ((f[i].st->pair[0] != nullptr) == with) {
+                at[k] = i;
+                g[k++] = f[i];
+            }
+        const fd_status st = advance_alike(g, k, s);
+        for (int j = 0; j < k; ++j) f[at[j]] = g[j];
         if (st != FD_OK) return st;
     }
     return FD_OK;

@@ -11,8 +11,11 @@ passed that step.  Latency = completion - arrival.
 
 The scheduling core (`Scheduler`) is device-agnostic: it drives any object
 with the methods of `TorchDevice` (footprint, start, advance, fence, done,
-wait, elapsed, finish, and optionally health), which lets the policy be
-tested on the CPU against a simulated device.  A shot whose wavefield ends
+wait, elapsed, finish, and optionally health and least_footprint), which lets
+the policy be tested on the CPU against a simulated device.  A device with
+least_footprint can start a request in less memory than footprint (here:
+without the second pair of levels, so that each of its steps is a launch); a
+request that does not fit the budget's rest otherwise is started that way.  A shot whose wavefield ends
 non-finite (NaN or infinity: a corrupted input or an overflow) fails alone:
 its outcome says so and the other shots of the mix are unaffected.
 """
@@ -124,6 +127,7 @@ class Scheduler:
         active: List[Any] = []          # device handles in the batch
         owner: Dict[int, Request] = {}  # id(handle) -> request
         stepped: Dict[int, int] = {}    # id(handle) -> steps enqueued
+        held: Dict[int, int] = {}       # id(handle) -> bytes of the budget
         inflight: collections.deque = collections.deque()  # (token, [handles done])
         used = 0
         out = {r.rid: Outcome(r.rid, r.arrival) for r in requests}
@@ -136,21 +140,24 @@ class Scheduler:
             # admission, FIFO: the head waits until it fits
             while waiting and len(active) < self.max_slots:
                 req = waiting[0]
-                fp = dev.footprint(req)
-                if used + fp > self.budget:
-                    if not active and not inflight and fp > self.budget:
+                fp = least = dev.footprint(req)
+                if used + fp > self.budget and hasattr(dev, "least_footprint"):
+                    least = dev.least_footprint(req)
+                if used + least > self.budget:
+                    if not active and not inflight and least > self.budget:
                         waiting.popleft()
                         out[req.rid].status = "failed: footprint exceeds the HBM budget"
                         continue
                     break
                 waiting.popleft()
                 try:
-                    h = dev.start(req)
+                    h = dev.start(req) if least == fp else dev.start(req, least=True)
                 except Exception as e:  # a bad request fails alone
                     out[req.rid].status = f"failed: {e}"
                     out[req.rid].finished = dev.elapsed()
                     continue
-                used += fp
+                used += least
+                held[id(h)] = least
                 owner[id(h)] = req
                 stepped[id(h)] = 0
                 out[req.rid].admitted = dev.elapsed()
@@ -182,7 +189,7 @@ class Scheduler:
                     err = dev.health(h) if hasattr(dev, "health") else None
                     o.status = "ok" if err is None else f"failed: {err}"
                     o.result = dev.finish(h)
-                    used -= dev.footprint(req)
+                    used -= held.pop(id(h))
                     n_done += 1
                 if finished and self.progress is not None:
                     self.progress(n_done, len(requests))
@@ -226,7 +233,7 @@ class TorchDevice:
         self.keep_traces = keep_traces
         self.stream = torch.cuda.current_stream()
         self.side = torch.cuda.Stream()
-        self._fp: Dict[int, int] = {}
+        self._fp: Dict[int, tuple] = {}
         self.t0_event = None
         self.t0_wall = 0.0
 
@@ -245,15 +252,23 @@ class TorchDevice:
             time.sleep(min(1e-3, max(0.0, t - self.elapsed())))
 
     def footprint(self, req: Request) -> int:
+        return self._footprints(req)[0]
+
+    def least_footprint(self, req: Request) -> int:
+        """The same without the state's second pair of levels."""
+        return self._footprints(req)[1]
+
+    def _footprints(self, req: Request):
         if req.rid not in self._fp:
             from . import Grid
             g = Grid(ndim=2, nz=req.nz, ny=1, nx=req.nx, dh=10.0, dt=1e-3)
-            s = self._abi.fd_query_bytes(g.c())
+            s = self._abi.fd_query_bytes(g.c(), 1, 1)
             nrec = req.nx
-            self._fp[req.rid] = int(s.model + s.state + req.nt * nrec * 4 + req.nz * req.nx * 4)
+            full = int(s.model + s.state + req.nt * nrec * 4 + req.nz * req.nx * 4)
+            self._fp[req.rid] = (full, full - int(s.checkpoints))   # a checkpoint is one pair of levels
         return self._fp[req.rid]
 
-    def start(self, req: Request):
+    def start(self, req: Request, least: bool = False):
         from . import Model
         # Inputs and model set-up on the side stream: fd_create_model waits
         # for the side stream only, never for the batch queued on the main
@@ -264,7 +279,7 @@ class TorchDevice:
             model = Model(grid, velocity, stream=self.side)
         model.buf.record_stream(self.stream)
         shot.wavelet.record_stream(self.stream)
-        state = model.new_state()
+        state = model.new_state(second_pair=not least)
         traces = torch.empty((shot.nt, shot.nrec), dtype=torch.float32,
                              device=velocity.device)
         h = dict(model=model, state=state, shot=shot, traces=traces, req=req)
