@@ -158,14 +158,21 @@ fd_status advance_group(Flight *f, int count, hipStream_t s)
 {
     int64_t run = 0;
     bool paired = true;
-    fdk::MultiGrid grids[FD_BATCH_MAX];
     for (int i = 0; i < count; ++i) {
         run = std::max(run, f[i].end - f[i].n);
         paired = paired && f[i].st->pair[0] != nullptr;
-        grids[i] = fdk::MultiGrid{(int)f[i].m->L.nz, f[i].m->L.px};
     }
-    const int steps = paired && run > 2 ? plan_multi(grids, count, run, fdk::kFwd, true).steps : 0;
+    int running = 0, steps = 0;
     while (run > 0) {
+        // planned anew when shots have ended, for those that still run
+        fdk::MultiGrid grids[FD_BATCH_MAX];
+        int now = 0;
+        for (int i = 0; i < count; ++i)
+            if (f[i].n < f[i].end) grids[now++] = fdk::MultiGrid{(int)f[i].m->L.nz, f[i].m->L.px};
+        if (now != running) {
+            running = now;
+            steps = paired && run > 2 ? plan_multi(grids, now, run, fdk::kFwd, true).steps : 0;
+        }
         if (steps > 0 && run > 2) {
             for (int half = 0; half < 2; ++half) {
                 fdk::MultiArgs it[FD_BATCH_MAX];
@@ -283,26 +290,22 @@ fd_status advance_alike(Flight *f, int count, hipStream_t s)
     return FD_OK;
 }
 
-// Shots with a second pair of levels, then those without: one that has none
-// must not make the others of a call take single steps.  (Where all take
-// single steps, they share the launches.)
+// The shots that still run: those with a second pair of levels, then those
+// without, since one that has none must not make the others of a call take
+// single steps.  (Where all take single steps, they share the launches.)
 fd_status advance(Flight *f, int count, hipStream_t s)
 {
     int64_t run = 0;
-    int paired = 0;
-    for (int i = 0; i < count; ++i) {
-        run = std::max(run, f[i].end - f[i].n);
-        paired += f[i].st->pair[0] != nullptr;
-    }
-    if (run <= 2 || paired == 0 || paired == count) return advance_alike(f, count, s);
+    for (int i = 0; i < count; ++i) run = std::max(run, f[i].end - f[i].n);
     for (const bool with : {true, false}) {
         Flight g[FD_BATCH_MAX];
         int at[FD_BATCH_MAX], k = 0;
         for (int i = 0; i < count; ++i)
-            if ((f[i].st->pair[0] != nullptr) == with) {
+            if (f[i].n < f[i].end && (run <= 2 || (f[i].st->pair[0] != nullptr) == with)) {
                 at[k] = i;
                 g[k++] = f[i];
             }
+        if (k == 0) continue;
         const fd_status st = advance_alike(g, k, s);
         for (int j = 0; j < k; ++j) f[at[j]] = g[j];
         if (st != FD_OK) return st;
