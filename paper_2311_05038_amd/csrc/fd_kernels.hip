@@ -10,9 +10,10 @@
 //   (256x8 cells for FP32 fields, 128x8 for 16-bit) and a chunk of `zc`
 //   planes; lanes stream along z (the slow axis) with a 9-deep register queue
 //   per cell, and x/y neighbours come from a double-buffered LDS copy of the
-//   current plane with a 4-cell halo.  Grids whose fields stay in the Infinity
-//   Cache, and the adjoint step, take 2 or 4 planes per block instead, all
-//   loads in flight at once (k_step3d_short).
+//   current plane with a 4-cell halo.  Most grids whose fields stay in the
+//   Infinity Cache, and most adjoint steps, take 2 or 4 planes per block
+//   instead, all loads in flight at once (k_step3d_short; fd_plan.hpp says
+//   where).
 // Both follow the fused step of arXiv 2311.05038, Section 7 (Listing 3's
 // add_source, fd_pzz, fd_pxx, fd_time and swap in one pass).
 #include <algorithm>
@@ -21,6 +22,7 @@
 
 #include "fd_device.hpp"
 #include "fd_launch.hpp"
+#include "fd_plan.hpp"
 
 // The 16-bit steps order their memory operations so that the next plane's
 // loads overlap the compute: the z sponge factor travels with the
@@ -786,8 +788,6 @@ __global__ __launch_bounds__(64 * NW) void k_step3d(StepArgs a)
 // --------------------------------------------------------------------------
 // 3D, grids too small to fill the device with long chunks
 // --------------------------------------------------------------------------
-constexpr int kShortTX = 64, kShortTY = 16;   // 16 lanes of 4 cells x 16 rows
-
 // The streaming kernel above keeps one plane of loads in flight per wave: on a
 // grid whose chunks are a few planes long it spends a memory latency on every
 // plane and eight on priming its queue (96 x 120 x 152: 12.5 us for 28 MB).
@@ -1416,18 +1416,7 @@ static int64_t resident_blocks_3d(int storage, bool cq, bool narrow)
 // streaming kernel with chunks of 16 rows is kept (2048 x 4096 binary16 23.1
 // us against 26.2, with 16-bit c 22.1 against 24.8).
 //
-// 3D FP32 also has the short kernel (k_step3d_short).  It is the faster one on
-// every measured grid up to 2^24.4 padded cells, whose fields (12 B per cell)
-// fit the 256 MB Infinity Cache (256^3 49-51 us against 50-54, 64 x 512^2 48
-// against 51, 128 x 512^2 102 against 96), with 2 planes per block below 12 M
-// cells and 4 above (100 x 200 x 300 23.0 / 23.8 us, 201 x 333 x 289 61.5 /
-// 58).  Beyond, with accesses that bypass the caches, it stays ahead for the
-// adjoint step (384^3 239 against 260 us, 512^3 560 against 562) and where
-// the streaming tiles are mostly padding (300^3 87 against 94).  With 16-bit
-// fields it pays up to 3 M padded cells (BF16, streaming / short: 48^3 9.7 /
-// 6.4 us, 66x480x49 16.9 / 10.0, 96x120x152 14.3 / 11.8); the streaming
-// kernel's fewer, longer blocks read the magnitude words and fold a maximum
-// less often, and larger grids keep it.
+// 3D also has the short kernel (k_step3d_short): short_plan says where.
 void plan_tiles(StepArgs &a, int ndim, int storage, int mode)
 {
     if (ndim == 2) {
@@ -1443,32 +1432,20 @@ void plan_tiles(StepArgs &a, int ndim, int storage, int mode)
         // the FP32 kernel (4: 256 wide, 2: 128 wide; the short kernel: 1, or 0
         // with accesses that bypass the caches)
         const bool narrow = storage == kF32 && narrow_tile_f32(a.nx, a.ny, a.nz);
-        if (storage == kF32) {
-            const int64_t cells = (int64_t)a.px * a.ny * a.nz;
-            const int64_t tile = narrow ? k3dTXN32 : k3dTXW32, width = (a.nx + tile - 1) / tile * tile;
-            const bool cached = cells <= 22000000;
-            if (cached || mode == kAdj || 100 * width > 115 * a.px) {
-                a.vx = cached ? 1 : 0;
-                a.zc = cells <= 12000000 ? 2 : 4;
-                a.tiles_x = (a.px + kShortTX - 1) / kShortTX;
-                a.tiles_y = (a.ny + kShortTY - 1) / kShortTY;
-                a.tiles_z = (a.nz + a.zc - 1) / a.zc;
-                return;
-            }
-        }
-        if (storage != kF32 && (int64_t)a.px * a.ny * a.nz <= 3000000) {
-            a.vx = 1;
-            a.zc = (int64_t)a.px * a.ny * a.nz <= 1000000 ? 2 : 4;
-            a.tiles_x = (a.px + kShortTX - 1) / kShortTX;
-            a.tiles_y = (a.ny + kShortTY - 1) / kShortTY;
-            a.tiles_z = (a.nz + a.zc - 1) / a.zc;
-            return;
-        }
         const int VX = storage == kF32 ? k3dVX32 : k3dVX16;
         const int RY = storage == kF32 ? (narrow ? k3dRYN32 : k3dRY32) : k3dRY16;
         const int NW = storage == kF32 ? FD_3D_NW32 : FD_3D_NW16;
         const int RPW = storage == kF32 ? (narrow ? k3dRPWN32 : FD_3D_RPW32) : FD_3D_RPW16;
         const int TX = 64 / RPW * VX, TY = NW * RPW * RY;
+        const ShortPlan sp = short_plan(a.nz, a.ny, a.nx, a.px, storage == kF32, mode == kAdj, TX, TY);
+        if (sp.zc > 0) {
+            a.vx = sp.stream ? 0 : 1;
+            a.zc = sp.zc;
+            a.tiles_x = (a.px + kShortTX - 1) / kShortTX;
+            a.tiles_y = (a.ny + kShortTY - 1) / kShortTY;
+            a.tiles_z = (a.nz + a.zc - 1) / a.zc;
+            return;
+        }
         a.vx = (int16_t)(TX / 64);
         a.tiles_x = (a.nx + TX - 1) / TX;
         a.tiles_y = (a.ny + TY - 1) / TY;
@@ -1508,16 +1485,14 @@ static void launch3d(const StepArgs &a, int nb, hipStream_t s)
             hipLaunchKernelGGL((k_step3d_short<kF32, 2, MODE, false, false>), dim3(nb), dim3(256), 0, s, a);
         else if (a.vx == 1)
             hipLaunchKernelGGL((k_step3d_short<kF32, 4, MODE, false, false>), dim3(nb), dim3(256), 0, s, a);
-        else if (a.vx == 0 || MODE == kAdj)   // (the plan gives the adjoint no other)
+        else if (a.vx == 0)
             hipLaunchKernelGGL((k_step3d_short<kF32, 4, MODE, false, true>), dim3(nb), dim3(256), 0, s, a);
-        else if constexpr (MODE != kAdj) {
-            if (a.vx * 64 == k3dTXN32)
-                hipLaunchKernelGGL((k_step3d<ST, k3dVX32, k3dRYN32, FD_3D_NW32, k3dRPWN32, MODE, false>), dim3(nb),
-                                   dim3(64 * FD_3D_NW32), 0, s, a);
-            else
-                hipLaunchKernelGGL((k_step3d<ST, k3dVX32, k3dRY32, FD_3D_NW32, FD_3D_RPW32, MODE, false>), dim3(nb),
-                                   dim3(64 * FD_3D_NW32), 0, s, a);
-        }
+        else if (a.vx * 64 == k3dTXN32)
+            hipLaunchKernelGGL((k_step3d<ST, k3dVX32, k3dRYN32, FD_3D_NW32, k3dRPWN32, MODE, false>), dim3(nb),
+                               dim3(64 * FD_3D_NW32), 0, s, a);
+        else
+            hipLaunchKernelGGL((k_step3d<ST, k3dVX32, k3dRY32, FD_3D_NW32, FD_3D_RPW32, MODE, false>), dim3(nb),
+                               dim3(64 * FD_3D_NW32), 0, s, a);
     }
     else if (a.vx == 1 && a.zc == 2)
         hipLaunchKernelGGL((k_step3d_short<ST, 2, MODE, CQ, false>), dim3(nb), dim3(256), 0, s, a);
