@@ -65,23 +65,47 @@ fd_status do_step(const fd_model *m, fd_state *st, const fd_shot *s, int64_t n, 
 struct MultiPlan {
     int steps;   // 0: no shape fits, or single steps are not slower
     double us;   // the run's modelled time
+    bool lone;   // (adjoint) one step of the run as a launch of its own
 };
 
 // A single step's time on `cells` padded cells, us (256^2 3.4, 1024^2 5.5,
 // 2048 x 4096 22.7): the launch, or the fields' 16 bytes per cell.
 double single_us(double cells) { return 3.2 + cells * 2.35e-6; }
+// The same of an adjoint step, which also reads the history and reads and
+// writes the FP64 sum, over cells covered by its 128-wide tiles: 256^2 4.0,
+// 1024^2 7.5, 2000^2 20.0, 8 x 1024^2 38.5 with one history field, and more
+// once many of them pass through the cache (28 bytes a cell besides).
+double single_adjoint_us(double cells) { return 4.6 + cells * (cells <= 9.0e6 ? 5.5e-6 : 6.6e-6); }
+
+// Cells whose two pairs of levels and c, 20 bytes a cell, stay in the 256 MB
+// Infinity Cache from one launch to the next.  A launch on more reads HBM and
+// takes 1.00 (16 shots of 1024^2) to 1.14 (2 of 2048 x 4096) of its modelled
+// time; kOutOfCache is the value that chose best over both and the mixes below.
+constexpr double kGroupCells = 13.0e6;
+constexpr double kOutOfCache = 1.08;
 
 // pairs: launches come in pairs that start and end on the same buffers, so a
 // run is cut into whole pairs of `steps` and a rest of one pair (or of one or
-// two single steps).  Otherwise launches follow one another freely.
+// two single steps).  Otherwise launches follow one another freely, as equal
+// as they can be; in the adjoint, where a lone step is the single step
+// kernel's, one may be split off if that is clearly less (5 steps of 2000^2:
+// 4 + 1 87 us, 2 + 3 115).
 MultiPlan plan_multi(const fdk::MultiGrid *grids, int count, int64_t run, int mode, bool pairs)
 {
-    double cells = 0.0;
-    for (int i = 0; i < count; ++i) cells += (double)grids[i].nz * grids[i].px;
-    MultiPlan best{0, pairs ? (double)run * single_us(cells) : 1e300};
+    double cells = 0.0, covered = 0.0;
+    for (int i = 0; i < count; ++i) {
+        cells += (double)grids[i].nz * grids[i].px;
+        covered += (double)grids[i].nz * ((grids[i].px + 127) / 128 * 128);
+    }
     double us[fdk::kMultiSteps + 1] = {0.0};
     for (int k = 1; k <= fdk::kMultiSteps; ++k)
         if (fdk::multi2d_shape(grids, count, k, mode, &us[k]) < 0) us[k] = 1e300;
+    if (mode == fdk::kAdj) us[1] = single_adjoint_us(covered);
+    auto equal = [&](int64_t m, int k) {
+        const int64_t n = (m + k - 1) / k;
+        return m == 0 ? 0.0 : (double)n * us[(m + n - 1) / n];
+    };
+    MultiPlan best{0, pairs ? (double)run * single_us(cells) : 1e300, false};
     for (int k = 1; k <= fdk::kMultiSteps && k <= run; ++k) {
         double t;
         if (pairs) {
@@ -89,11 +113,15 @@ MultiPlan plan_multi(const fdk::MultiGrid *grids, int count, int64_t run, int mo
             t = (double)(run / (2 * k)) * 2.0 * us[k];
             t += rest <= 2 ? (double)rest * single_us(cells) : us[(rest + 1) / 2] + us[rest / 2];
         } else {
-            const int64_t n = (run + k - 1) / k;
-            t = (double)n * us[(run + n - 1) / n];
+            t = equal(run, k);
         }
-        if (t < best.us) best = MultiPlan{k, t};
+        if (t < best.us) best = MultiPlan{k, t, false};
     }
+    if (mode == fdk::kAdj)
+        for (int k = 2; k <= fdk::kMultiSteps && k < run; ++k) {
+            const double t = equal(run - 1, k) + us[1];
+            if (t < (best.lone ? 1.0 : 0.9) * best.us) best = MultiPlan{k, t, true};
+        }
     return best;
 }
 
@@ -142,13 +170,6 @@ fd_status keep_levels(const Flight &f, hipStream_t s)
         e = hipMemcpyAsync((char *)f.keep + bytes, f.st->buf[(f.n + 1) & 1], bytes, hipMemcpyDeviceToDevice, s);
     return e == hipSuccess ? FD_OK : hip_fail(e, "checkpoint copy");
 }
-
-// Cells whose two pairs of levels and c, 20 bytes a cell, stay in the 256 MB
-// Infinity Cache from one launch to the next.  A launch on more reads HBM and
-// takes 1.00 (16 shots of 1024^2) to 1.14 (2 of 2048 x 4096) of its modelled
-// time; kOutOfCache is the value that chose best over both and the mixes below.
-constexpr double kGroupCells = 13.0e6;
-constexpr double kOutOfCache = 1.08;
 
 // Steps every flight to its end.  Launches of several steps come in pairs:
 // the first writes the state's second pair of levels, the next one writes
@@ -241,7 +262,7 @@ fd_status advance_group(Flight *f, int count, hipStream_t s)
                 }
             }
             if (count > 1) {
-                const hipError_t e = fdk::launch_step_batch2d(b, s);
+                const hipError_t e = fdk::launch_step_batch2d(b, fdk::kFwd, s);
                 if (e != hipSuccess) return hip_fail(e, "batched step launch");
             }
             for (int i = 0; i < count; ++i)
@@ -694,16 +715,28 @@ struct ShotIO {
     void *work;
 };
 
-// The cut of `m` steps into launches for the backward pass: at most `cap`
-// steps each, the larger ones last; `even`: an even number of launches, or
-// one.
-std::vector<int> cut_steps(int64_t m, int cap, bool even)
+// The cut of `m` steps into `n` launches for the backward pass: at most `cap`
+// steps each, the larger ones last; `even`: an even number of launches, or one.
+struct Cut {
+    int64_t m, n;
+    Cut(int64_t steps, int cap, bool even) : m(steps), n((steps + cap - 1) / cap)
+    {
+        if (even && n > 1 && (n & 1)) ++n;
+    }
+    int steps(int64_t i) const { return (int)(m / n + (i >= n - m % n ? 1 : 0)); }
+};
+
+// Whether a first launch of the image's recompute, of k < 2 steps on `count`
+// shots, is better done as copies of the checkpoints' P to the history (3.3 us
+// each and 8 bytes a cell at 7 TB/s) and a single step: per step of a lone
+// 2000^2 shot with a checkpoint at every step 51 -> 30 us.
+bool copies_first(const fdk::MultiGrid *grids, int count, int k)
 {
-    int64_t n = (m + cap - 1) / cap;
-    if (even && n > 1 && (n & 1)) ++n;
-    std::vector<int> out;
-    for (int64_t i = 0; i < n; ++i) out.push_back((int)(m / n + (i >= n - m % n ? 1 : 0)));
-    return out;
+    const double cells = (double)grids[0].nz * grids[0].px, all = count * cells;
+    double us = 0.0;
+    (void)fdk::multi2d_shape(grids, count, k, fdk::kFwdKeep, &us);
+    us = std::max(us, 2.5 + all * 2.6e-6);
+    return count * (3.3 + cells * 1.15e-6) + (k > 0 ? single_us(all) : 0.0) < us;
 }
 
 const char *ckpt_slot(const Layout &L, const void *ckpt, int64_t seg)
@@ -716,15 +749,19 @@ const char *ckpt_slot(const Layout &L, const void *ckpt, int64_t seg)
 // address decides).
 bool vector_aligned(const void *p) { return (uintptr_t)p % 16 == 0; }
 
-// backward_pass on 2D grids, up to FD_BATCH_MAX shots: several steps per launch.  Two pairs of levels,
-// the recompute state's and the adjoint state's places in the work buffers,
-// serve the adjoint recursion in turn; while a segment is recomputed, the one
-// that does not hold the adjoint state serves the recompute, which reads the
-// checkpoint where it lies.  The gradient's recompute needs a second pair of
-// its own (the image's does not: its levels go to the history) and takes the
-// segment's last two history fields, which only its last launch writes: that
-// one reads the first pair, since the launches are even in number, and it
-// stores no levels.
+// backward_pass on 2D grids, up to FD_BATCH_MAX shots: several steps per
+// launch.  Two pairs of levels, the recompute state's and the adjoint state's
+// places in the work buffers, serve the adjoint recursion in turn; while a
+// segment is recomputed, the one that does not hold the adjoint state serves
+// the recompute, which reads the checkpoint where it lies.  The gradient's
+// recompute needs a second pair of its own (the image's does not: its levels
+// go to the history) and takes the segment's last two history fields, which
+// only its last launch writes: that one reads the first pair, since the
+// launches are even in number, and it stores no levels.
+//
+// A lone step of the adjoint or of the image's recompute is the single step
+// kernel's, which has no halo to compute and loads each field once (2000 x
+// 2000: adjoint 18 us against 36, recompute 13 against 25).
 fd_status backward_2d(const fd_model *model, const ShotIO *io, int32_t count, int32_t every, bool image,
                       hipStream_t s)
 {
@@ -735,72 +772,106 @@ fd_status backward_2d(const fd_model *model, const ShotIO *io, int32_t count, in
     };
     auto hist = [&](int32_t i, int64_t slot) -> float * { return (float *)io[i].work + (2 + slot) * fl; };
     const int64_t nt = io[0].shot->nt, nseg = n_ckpt(nt, every);
-    const int32_t group = count;   // at most FD_BATCH_MAX
-    std::vector<fdk::MultiGrid> grids((size_t)group, fdk::MultiGrid{(int)L.nz, L.px});
-    // (the recompute's at least 2, so that its last launch writes both fields
-    // of the tail)
-    auto most = [&](int64_t run, int mode) { return std::max(1, plan_multi(grids.data(), group, run, mode, false).steps); };
+    fdk::MultiGrid grids[FD_BATCH_MAX];
+    std::fill(grids, grids + count, fdk::MultiGrid{(int)L.nz, L.px});
+    auto most = [&](int64_t run, int mode) { return std::max(1, plan_multi(grids, count, run, mode, false).steps); };
     const int64_t seg0 = std::min<int64_t>(nt, every);
-    const int cap = std::max(2, most(seg0, image ? fdk::kFwdKeep : fdk::kFwdLap)), cap_adj = most(seg0, fdk::kAdj);
+    // (the gradient's at least 2, so that its last launch writes both fields
+    // of the tail)
+    const int cap = std::max(2, most(seg0, image ? fdk::kFwdKeep : fdk::kFwdLap));
     auto launch = [&](auto make_args, int mode) -> hipError_t {
         fdk::MultiArgs it[FD_BATCH_MAX];
         for (int32_t i = 0; i < count; ++i) it[i] = make_args(i);
         return fdk::launch_multi2d(it, count, mode, s);
     };
-    int zp = 1;   // the pair that holds the adjoint state: (z^(k+1), z^(k+2))
+    auto launch_single = [&](auto make_args, int mode) -> hipError_t {
+        if (count == 1) return fdk::launch_step(make_args(0), 2, L.storage, mode, s);
+        fdk::Batch2D b;
+        b.count = count;
+        for (int32_t i = 0; i < count; ++i) b.it[i] = make_args(i);
+        return fdk::launch_step_batch2d(b, mode, s);
+    };
+    // the pair that holds the adjoint state, and which of its levels is
+    // z^(k+1) (the other is z^(k+2))
+    int zp = 1, zi = 0;
     for (int64_t seg = nseg - 1; seg >= 0; --seg) {
         const int64_t n0 = seg * every, n1 = std::min<int64_t>(nt, n0 + every), m = n1 - n0;
-        const std::vector<int> cut = !image ? cut_steps(m, cap, true)
-                                     : m > 1 ? cut_steps(m - 1, cap, false) : std::vector<int>(1, 0);
-        // The kernel reads 16 bytes at a time: a checkpoint at an address that
+        const Cut cut = image ? Cut(m - 1, cap, false) : Cut(m, cap, true);
+        // The kernels read 16 bytes at a time: a checkpoint at an address that
         // does not allow it is copied first, to levels that the launch reading
         // it does not write (the gradient's launch 0 of several writes the
         // free pair, and not the history's last two fields).
         auto restored = [&](int32_t i, int which) -> float * {
-            return image || cut.size() == 1 ? level(i, 1 - zp, which) : hist(i, m - 2 + which);
+            return image || cut.n == 1 ? level(i, 1 - zp, which) : hist(i, m - 2 + which);
         };
-        auto saved = [&](int32_t i, int which) -> const float * {
+        auto saved = [&](int32_t i, int which) -> float * {
             if (!vector_aligned(io[i].ckpt)) return restored(i, which);
-            return (const float *)(ckpt_slot(L, io[i].ckpt, seg) + which * L.field);
+            return (float *)(ckpt_slot(L, io[i].ckpt, seg) + which * L.field);
+        };
+        auto copy = [&](float *to, int32_t i, int which) {
+            return hipMemcpyAsync(to, ckpt_slot(L, io[i].ckpt, seg) + which * L.field, L.field,
+                                  hipMemcpyDeviceToDevice, s);
         };
         for (int32_t i = 0; i < count; ++i) {
             if (vector_aligned(io[i].ckpt)) continue;
             for (int which = 0; which < 2; ++which) {
-                const hipError_t e = hipMemcpyAsync(restored(i, which), ckpt_slot(L, io[i].ckpt, seg) + which * L.field,
-                                                    L.field, hipMemcpyDeviceToDevice, s);
+                const hipError_t e = copy(restored(i, which), i, which);
                 if (e != hipSuccess) return hip_fail(e, "checkpoint restore");
             }
         }
+        int64_t p = 0;
         if (image) {
-            // slot p holds w^(n0+p); slot 0 is the checkpoint's P
-            int64_t p = 0;
-            for (const int k : cut) {
-                const hipError_t e = launch(
-                    [&](int32_t i) {
-                        fdk::MultiArgs a = multi_args(model, io[i].shot, n0 + p, k);
-                        a.cur = p == 0 ? saved(i, 0) : hist(i, p);
-                        a.prev = p == 0 ? saved(i, 1) : hist(i, p - 1);
-                        if (p == 0) a.keep1 = hist(i, 0);
-                        a.hist = k > 0 ? hist(i, p + 1) : nullptr;
-                        a.hist_stride = fl;
-                        return a;
-                    },
-                    fdk::kFwdKeep);
+            // slot p holds w^(n0+p); slot 0 is the checkpoint's P, copied or
+            // stored by the first launch
+            const int k0 = cut.n == 0 ? 0 : cut.steps(0);
+            const bool copied = k0 < 2 && copies_first(grids, count, k0);
+            if (copied)
+                for (int32_t i = 0; i < count; ++i) {
+                    const hipError_t e = copy(hist(i, 0), i, 0);
+                    if (e != hipSuccess) return hip_fail(e, "checkpoint restore");
+                }
+            for (int64_t l = 0; l < cut.n || (l == 0 && !copied); ++l) {
+                const int k = l == 0 ? k0 : cut.steps(l);
+                auto cur = [&](int32_t i) { return p == 0 ? saved(i, 0) : hist(i, p); };
+                auto prev = [&](int32_t i) { return p == 0 ? saved(i, 1) : hist(i, p - 1); };
+                const hipError_t e =
+                    k == 1 && (l > 0 || copied)
+                        ? launch_single(
+                              [&](int32_t i) {
+                                  StepArgs a = base_args(model, io[i].shot);
+                                  a.cur = cur(i);
+                                  a.prev = prev(i);
+                                  a.out = hist(i, p + 1);
+                                  a.n = n0 + p;
+                                  return a;
+                              },
+                              fdk::kFwd)
+                        : launch(
+                              [&](int32_t i) {
+                                  fdk::MultiArgs a = multi_args(model, io[i].shot, n0 + p, k);
+                                  a.cur = cur(i);
+                                  a.prev = prev(i);
+                                  if (p == 0) a.keep1 = hist(i, 0);
+                                  a.hist = k > 0 ? hist(i, p + 1) : nullptr;
+                                  a.hist_stride = fl;
+                                  return a;
+                              },
+                              fdk::kFwdKeep);
                 if (e != hipSuccess) return hip_fail(e, "recompute steps");
                 p += k;
             }
         } else {
-            int64_t p = 0;
-            for (size_t l = 0; l < cut.size(); ++l) {
-                const bool last = l + 1 == cut.size();
+            for (int64_t l = 0; l < cut.n; ++l) {
+                const int k = cut.steps(l);
+                const bool last = l + 1 == cut.n;
                 // launch 0 reads the checkpoint; odd launches read the free
                 // pair, even ones the history's last two fields
-                auto place = [&](int32_t i, size_t after, int which) -> float * {
+                auto place = [&](int32_t i, int64_t after, int which) -> float * {
                     return (after & 1) == 0 ? level(i, 1 - zp, which) : hist(i, m - 2 + which);
                 };
                 const hipError_t e = launch(
                     [&](int32_t i) {
-                        fdk::MultiArgs a = multi_args(model, io[i].shot, n0 + p, cut[l]);
+                        fdk::MultiArgs a = multi_args(model, io[i].shot, n0 + p, k);
                         a.cur = l == 0 ? saved(i, 0) : place(i, l - 1, 0);
                         a.prev = l == 0 ? saved(i, 1) : place(i, l - 1, 1);
                         if (!last) {
@@ -813,30 +884,57 @@ fd_status backward_2d(const fd_model *model, const ShotIO *io, int32_t count, in
                     },
                     fdk::kFwdLap);
                 if (e != hipSuccess) return hip_fail(e, "recompute steps");
-                p += cut[l];
+                p += k;
             }
         }
         int64_t k = n1;   // adjoint steps k = n1 .. n0+1
-        for (const int c : cut_steps(m, cap_adj, false)) {
-            const hipError_t e = launch(
-                [&](int32_t i) {
-                    fdk::MultiArgs a = multi_args(model, io[i].shot, 0, c);
-                    const int64_t nrec = nrec_of(io[i].shot);
-                    a.nt = 0;  // no source in the adjoint recursion
-                    a.cur = level(i, zp, 0);
-                    a.prev = level(i, zp, 1);
-                    a.out1 = level(i, 1 - zp, 0);
-                    a.out0 = level(i, 1 - zp, 1);
-                    a.resid = nrec > 0 ? io[i].adj + (size_t)(k - 1) * (size_t)nrec : nullptr;
-                    a.rec_stride = -nrec;
-                    a.hist = hist(i, k - 1 - n0);
-                    a.hist_stride = -fl;
-                    a.g = (double *)((float *)io[i].work + (4 + every) * fl);
-                    return a;
-                },
-                fdk::kAdj);
-            if (e != hipSuccess) return hip_fail(e, "adjoint steps");
-            zp = 1 - zp;
+        const MultiPlan plan = plan_multi(grids, count, m, fdk::kAdj, false);
+        const Cut back(plan.lone ? m - 1 : m, std::max(1, plan.steps), false);
+        for (int64_t l = 0; k > n0; ++l) {
+            const int c = l < back.n ? back.steps(l) : 1;
+            // (nt = 0: no source in the adjoint recursion)
+            auto resid = [&](int32_t i) -> const float * {
+                const int64_t nrec = nrec_of(io[i].shot);
+                return nrec > 0 ? io[i].adj + (size_t)(k - 1) * (size_t)nrec : nullptr;
+            };
+            auto sum = [&](int32_t i) { return (double *)((float *)io[i].work + (4 + every) * fl); };
+            if (c == 1) {   // z^k takes the place of z^(k+2)
+                const hipError_t e = launch_single(
+                    [&](int32_t i) {
+                        StepArgs a = base_args(model, io[i].shot);
+                        a.cur = level(i, zp, zi);
+                        a.prev = level(i, zp, 1 - zi);
+                        a.n = k;
+                        a.nt = 0;
+                        a.lap = hist(i, k - 1 - n0);
+                        a.resid_row = resid(i);
+                        a.g = sum(i);
+                        return a;
+                    },
+                    fdk::kAdj);
+                if (e != hipSuccess) return hip_fail(e, "adjoint steps");
+                zi = 1 - zi;
+            } else {
+                const hipError_t e = launch(
+                    [&](int32_t i) {
+                        fdk::MultiArgs a = multi_args(model, io[i].shot, 0, c);
+                        a.nt = 0;
+                        a.cur = level(i, zp, zi);
+                        a.prev = level(i, zp, 1 - zi);
+                        a.out1 = level(i, 1 - zp, 0);
+                        a.out0 = level(i, 1 - zp, 1);
+                        a.resid = resid(i);
+                        a.rec_stride = -nrec_of(io[i].shot);
+                        a.hist = hist(i, k - 1 - n0);
+                        a.hist_stride = -fl;
+                        a.g = sum(i);
+                        return a;
+                    },
+                    fdk::kAdj);
+                if (e != hipSuccess) return hip_fail(e, "adjoint steps");
+                zp = 1 - zp;
+                zi = 0;
+            }
             k -= c;
         }
     }

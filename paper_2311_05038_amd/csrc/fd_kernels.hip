@@ -341,9 +341,10 @@ __global__ __launch_bounds__(64) void k_step2d(StepArgs a)
 // FP32 256^2 4.5 -> 3.4 us, 1024^2 7.8 -> 5.4, 1201 x 1747 10.5 -> 8.6, 2048 x
 // 4096 23.9 -> 22.7; BF16 256^2 7.6 -> 5.2, 1024^2 12.5 -> 7.3, 1201 x 1747
 // 12.8 -> 9.4.)
-template <int ST, int RZ, bool CQ>
+template <int ST, int RZ, int MODE, bool CQ>
 __device__ __forceinline__ void step2d_block(const StepArgs &a, int tx, int tz, float *pl, bool block0, int32_t *red)
 {
+    static_assert(ST == kF32 || MODE == kFwd, "16-bit fields: forward steps");
     using T = typename Stor<ST>::T;
     using CT = std::conditional_t<CQ, uint16_t, float>;
     using PT = Pack<T, 4>;
@@ -388,7 +389,8 @@ __device__ __forceinline__ void step2d_block(const StepArgs &a, int tx, int tz, 
 #pragma unroll
     for (int r = 0; r < RZ; ++r) gz[r] = z0 + r < nz ? a.gz[z0 + r] : 0.0f;
     float inj = 0.0f;
-    if (a.n + 1 < a.nt) inj = a.amp * a.wavelet[a.n + 1];
+    if constexpr (MODE != kAdj)
+        if (a.n + 1 < a.nt) inj = a.amp * a.wavelet[a.n + 1];
     const HalfCtx h = half_prologue<ST>(a, inj, block0);
 
     auto put = [&](int at_l, const PT &p) {
@@ -456,28 +458,29 @@ __device__ __forceinline__ void step2d_block(const StepArgs &a, int tx, int tz, 
                 lap = fmaf(2.0f * kA0, u, lz8 + lx8);
             }
             nw[v] = update<ST>(G[v], u, cc[v], lap, pc[v], h);
-            lp[v] = lap;
+            lp[v] = MODE == kAdj ? u : lap;
         }
         Outgoing<T, 4> out;
-        finish_cells<ST, 4, kFwd, false, false>(a, h, z0 + r, 0, x0, xin && z0 + r < nz, (size_t)(z0 + r) * px,
+        finish_cells<ST, 4, MODE, false, false>(a, h, z0 + r, 0, x0, xin && z0 + r < nz, (size_t)(z0 + r) * px,
                                                 (uint32_t)x0, nw, lp, pc, cc, G, inj, bmax, out);
-        flush<T, 4, kFwd, false>(out);
+        flush<T, 4, MODE, false>(out);
     }
     if constexpr (ST != kF32)
         block_max_to<256>(max_slot(a.meta, (int)((a.n + 1) & 3)), bmax * h.sn, (float *)red);
 }
 
-template <int ST, int RZ, bool CQ>
+template <int ST, int RZ, int MODE, bool CQ>
 __global__ __launch_bounds__(256) void k_step2d_block(StepArgs a)
 {
     __shared__ __attribute__((aligned(16))) float pl[(8 * RZ + 8) * 136];
     __shared__ int32_t red[4];
     const int t = xcd_tile(blockIdx.x, a.tiles_x * a.tiles_z);
-    step2d_block<ST, RZ, CQ>(a, t % a.tiles_x, t / a.tiles_x, pl, blockIdx.x == 0, red);
+    step2d_block<ST, RZ, MODE, CQ>(a, t % a.tiles_x, t / a.tiles_x, pl, blockIdx.x == 0, red);
 }
 
 // Batched 2D FP32 step: block b belongs to the item whose tile range holds
 // b; every item keeps its own grid, fields and step index.
+template <int MODE>
 __global__ __launch_bounds__(256) void k_step2d_batch(Batch2D b)
 {
     __shared__ __attribute__((aligned(16))) float pl[(8 + 8) * 136];
@@ -486,7 +489,7 @@ __global__ __launch_bounds__(256) void k_step2d_batch(Batch2D b)
     while (i + 1 < b.count && t >= b.begin[i + 1]) ++i;
     const StepArgs &a = b.it[i];
     const int lt = t - b.begin[i];
-    step2d_block<kF32, 1, false>(a, lt % a.tiles_x, lt / a.tiles_x, pl, false, nullptr);
+    step2d_block<kF32, 1, MODE, false>(a, lt % a.tiles_x, lt / a.tiles_x, pl, false, nullptr);
 }
 
 // --------------------------------------------------------------------------
@@ -1503,15 +1506,15 @@ static void launch3d(const StepArgs &a, int nb, hipStream_t s)
                            dim3(64 * FD_3D_NW16), 0, s, a);
 }
 
-template <int ST, bool CQ>
+template <int ST, int MODE = kFwd, bool CQ = false>
 static void launch2d(const StepArgs &a, int nb, hipStream_t s)
 {
     if constexpr (ST == kF32) {
-        hipLaunchKernelGGL((k_step2d_block<ST, 1, CQ>), dim3(nb), dim3(256), 0, s, a);
+        hipLaunchKernelGGL((k_step2d_block<ST, 1, MODE, CQ>), dim3(nb), dim3(256), 0, s, a);
     } else {
-        if (a.vx == 1) hipLaunchKernelGGL((k_step2d_block<ST, 1, CQ>), dim3(nb), dim3(256), 0, s, a);
-        else if (a.vx == 2) hipLaunchKernelGGL((k_step2d_block<ST, 2, CQ>), dim3(nb), dim3(256), 0, s, a);
-        else if (a.vx == 4) hipLaunchKernelGGL((k_step2d_block<ST, 4, CQ>), dim3(nb), dim3(256), 0, s, a);
+        if (a.vx == 1) hipLaunchKernelGGL((k_step2d_block<ST, 1, MODE, CQ>), dim3(nb), dim3(256), 0, s, a);
+        else if (a.vx == 2) hipLaunchKernelGGL((k_step2d_block<ST, 2, MODE, CQ>), dim3(nb), dim3(256), 0, s, a);
+        else if (a.vx == 4) hipLaunchKernelGGL((k_step2d_block<ST, 4, MODE, CQ>), dim3(nb), dim3(256), 0, s, a);
         else hipLaunchKernelGGL((k_step2d<ST, 2, CQ>), dim3(nb), dim3(64), 0, s, a);
     }
 }
@@ -1520,17 +1523,18 @@ hipError_t launch_step(StepArgs a, int ndim, int storage, int mode, hipStream_t 
 {
     // 16-bit c is built for the forward step on 16-bit fields only
     if (a.c16 != nullptr && (storage == kF32 || mode != kFwd)) return hipErrorInvalidValue;
-    // the history and adjoint modes in 2D are launch_multi2d's
-    if (ndim == 2 && mode != kFwd) return hipErrorInvalidValue;
+    // a recompute that keeps L(cur) is launch_multi2d's in 2D
+    if (ndim == 2 && (mode == kFwdLap || (storage != kF32 && mode != kFwd))) return hipErrorInvalidValue;
     plan_tiles(a, ndim, storage, mode);
     const int nb = a.tiles_x * a.tiles_y * a.tiles_z;
     if (ndim == 2) {
         const bool cq = a.c16 != nullptr;
-        if (storage == kF32) launch2d<kF32, false>(a, nb, s);
-        else if (storage == kF16 && cq) launch2d<kF16, true>(a, nb, s);
-        else if (storage == kF16) launch2d<kF16, false>(a, nb, s);
-        else if (cq) launch2d<kBF16, true>(a, nb, s);
-        else launch2d<kBF16, false>(a, nb, s);
+        if (storage == kF32 && mode == kAdj) launch2d<kF32, kAdj>(a, nb, s);
+        else if (storage == kF32) launch2d<kF32>(a, nb, s);
+        else if (storage == kF16 && cq) launch2d<kF16, kFwd, true>(a, nb, s);
+        else if (storage == kF16) launch2d<kF16>(a, nb, s);
+        else if (cq) launch2d<kBF16, kFwd, true>(a, nb, s);
+        else launch2d<kBF16>(a, nb, s);
     } else {
         if (storage == kF32) {
             if (mode == kFwd) launch3d<kF32, kFwd>(a, nb, s);
@@ -1547,17 +1551,19 @@ hipError_t launch_step(StepArgs a, int ndim, int storage, int mode, hipStream_t 
     return hipGetLastError();
 }
 
-hipError_t launch_step_batch2d(Batch2D &b, hipStream_t s)
+hipError_t launch_step_batch2d(Batch2D &b, int mode, hipStream_t s)
 {
+    if (mode != kFwd && mode != kAdj) return hipErrorInvalidValue;
     int total = 0;
     for (int i = 0; i < b.count; ++i) {
-        plan_tiles(b.it[i], 2, kF32, kFwd);
+        plan_tiles(b.it[i], 2, kF32, mode);
         b.begin[i] = total;
         total += b.it[i].tiles_x * b.it[i].tiles_z;
     }
     b.begin[b.count] = total;
     if (total == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_step2d_batch, dim3(total), dim3(256), 0, s, b);
+    if (mode == kAdj) hipLaunchKernelGGL(k_step2d_batch<kAdj>, dim3(total), dim3(256), 0, s, b);
+    else hipLaunchKernelGGL(k_step2d_batch<kFwd>, dim3(total), dim3(256), 0, s, b);
     return hipGetLastError();
 }
 

@@ -32,7 +32,8 @@ struct MultiBatch {
 static_assert(sizeof(MultiBatch<kBatchMax>) <= 4096, "batched multi-step arguments must fit the kernel-argument segment");
 
 hipError_t launch_step(StepArgs a, int ndim, int storage, int mode, hipStream_t s);
-hipError_t launch_step_batch2d(Batch2D &b, hipStream_t s);
+// 2D FP32, kFwd or kAdj
+hipError_t launch_step_batch2d(Batch2D &b, int mode, hipStream_t s);
 // Several steps of up to kBatchMax 2D FP32 grids in one launch (modes kFwd,
 // kFwdLap, kFwdKeep, kAdj); every item takes its own number of steps, at most
 // kMultiSteps.

@@ -38,3 +38,23 @@ def test_the_rest_of_a_batch_is_planned_for_the_shots_that_run():
     lone = [_flight(256, 256, 391)]
     rest = _launches(lambda s: fd.step_batch(lone, 391, stream=s))
     assert together <= n + rest + 4     # a pair of launches may straddle the end
+
+
+@pytest.mark.parametrize("nz,nx,count,copied", [(2000, 2000, 1, True), (1000, 1000, 1, True), (100, 100, 8, False)])
+def test_an_image_with_a_checkpoint_at_every_step(nz, nx, count, copied):
+    """The history is the checkpoints' P: a copy, unless many small shots share
+    the launch that stores it."""
+    import torch
+    from helpers import setup
+    from test_gpu_state_levels import _problem
+    nt = 4
+    model, state, shot = setup(_problem(nz, nx, nt))
+    ck = model.checkpoint_buffer(nt, 1)
+    tr = model.run_shot(state, shot, ckpt=ck, ckpt_every=1)
+    need = model.sizes_for(nt, 1).adjoint_work
+    works = [torch.empty(need, dtype=torch.uint8, device="cuda") for _ in range(count)]
+    img = torch.zeros(nz * nx, dtype=torch.float64, device="cuda")
+
+    def call(s):
+        model.rtm_image_shots([shot] * count, [tr] * count, [ck] * count, 1, img, works=works, stream=s)
+    assert _launches(call, copies=True) == (nt * count if copied else 0)

@@ -18,8 +18,9 @@ def _problem(nz, nx, nt, seed=4):
                       sponge_faces=0x3E, velocity_kind="random", velocity_seed=seed)
 
 
-def _launches(call):
-    """Nodes of the graph that `call(stream)` records; nothing runs."""
+def _launches(call, copies=False):
+    """Nodes (or only the copies) of the graph that `call(stream)` records;
+    nothing runs."""
     import torch
     path = next(w for line in open("/proc/self/maps") for w in line.split() if "libamdhip64" in w)
     hip = ctypes.CDLL(path)
@@ -31,8 +32,14 @@ def _launches(call):
     call(s)
     assert hip.hipStreamEndCapture(raw, ctypes.byref(g)) == 0
     assert hip.hipGraphGetNodes(g, None, ctypes.byref(n)) == 0
+    nodes, kind = (ctypes.c_void_p * max(1, n.value))(), ctypes.c_int()
+    assert hip.hipGraphGetNodes(g, nodes, ctypes.byref(n)) == 0
+    memcpys = 0
+    for node in nodes[:n.value]:
+        assert hip.hipGraphNodeGetType(ctypes.c_void_p(node), ctypes.byref(kind)) == 0
+        memcpys += kind.value == 1
     assert hip.hipGraphDestroy(g) == 0
-    return n.value
+    return memcpys if copies else n.value
 
 
 def _flight(nz, nx, nt, second_pair=True, seed=4):
