@@ -98,8 +98,12 @@ MultiPlan plan_multi(const fdk::MultiGrid *grids, int count, int64_t run, int mo
         covered += (double)grids[i].nz * ((grids[i].px + 127) / 128 * 128);
     }
     double us[fdk::kMultiSteps + 1] = {0.0};
-    for (int k = 1; k <= fdk::kMultiSteps; ++k)
+    for (int k = 1; k <= fdk::kMultiSteps; ++k) {
         if (fdk::multi2d_shape(grids, count, k, mode, &us[k]) < 0) us[k] = 1e300;
+        // beyond the cache a launch of few steps is bound by its 24 bytes a
+        // cell (3000 x 5000: 1 + 2 steps 131 us, three single steps 115)
+        if (cells > kGroupCells) us[k] = std::max(us[k], 2.5 + cells * 3.8e-6);
+    }
     if (mode == fdk::kAdj) us[1] = single_adjoint_us(covered);
     auto equal = [&](int64_t m, int k) {
         const int64_t n = (m + k - 1) / k;
@@ -299,9 +303,11 @@ fd_status advance_alike(Flight *f, int count, hipStream_t s)
             double sum = (double)f[i++].m->L.npad;
             while (i < count && sum + 0.5 * (double)f[i].m->L.npad <= share && sum + (double)f[i].m->L.npad <= kGroupCells)
                 sum += (double)f[i++].m->L.npad;
-            grouped += plan_multi(grids + i0, i - i0, run, fdk::kFwd, true).us * (sum > kGroupCells ? kOutOfCache : 1.0);
+            const MultiPlan part = plan_multi(grids + i0, i - i0, run, fdk::kFwd, true);
+            grouped += part.us * (part.steps > 0 && sum > kGroupCells ? kOutOfCache : 1.0);
         }
-        if (plan_multi(grids, count, run, fdk::kFwd, true).us * kOutOfCache <= grouped) groups = 0;
+        const MultiPlan whole = plan_multi(grids, count, run, fdk::kFwd, true);
+        if (whole.us * (whole.steps > 0 ? kOutOfCache : 1.0) <= grouped) groups = 0;
     }
     if (groups == 0) first[groups = 1] = count;
     for (int g = 0; g < groups; ++g) {

@@ -40,6 +40,17 @@ def test_the_rest_of_a_batch_is_planned_for_the_shots_that_run():
     assert together <= n + rest + 4     # a pair of launches may straddle the end
 
 
+def test_few_steps_beyond_the_cache_are_single_steps():
+    """Launches of one or two steps move more bytes there than they save."""
+    import torch
+    from helpers import setup
+    from test_gpu_state_levels import _problem
+    model, state, shot = setup(_problem(3000, 5000, 3))
+    tr = torch.empty((3, shot.nrec), device="cuda")
+    # a clear, the source, three steps
+    assert _launches(lambda s: model.run_shot(state, shot, tr, stream=s)) == 5
+
+
 @pytest.mark.parametrize("nz,nx,count,copied", [(2000, 2000, 1, True), (1000, 1000, 1, True), (100, 100, 8, False)])
 def test_an_image_with_a_checkpoint_at_every_step(nz, nx, count, copied):
     """The history is the checkpoints' P: a copy, unless many small shots share
