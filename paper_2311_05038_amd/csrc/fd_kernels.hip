@@ -186,19 +186,19 @@ __device__ __forceinline__ float update(float G, float ctr, float c, float lap, 
 // --------------------------------------------------------------------------
 // 2D
 // --------------------------------------------------------------------------
-// CQ: c is read as 16-bit fixed-point codes (16-bit fields, forward step).
-// The streaming 2D step (16-bit fields on the largest grids): one wave takes
-// 64 VX columns and `zc` rows.
-template <int ST, int VX, bool CQ>
+// The streaming 2D step (16-bit fields on the largest grids, forward): one
+// wave takes 128 columns and `zc` rows.  CQ: c is read as 16-bit fixed-point
+// codes.
+constexpr int k2dVX = 2;
+template <int ST, bool CQ>
 __device__ __forceinline__ void step2d_tile(const StepArgs &a, int tx, int tz,
-                                            float (*row)[64 * VX + 8], const HalfCtx &h,
+                                            float (*row)[64 * k2dVX + 8], const HalfCtx &h,
                                             float inj, float &bmax)
 {
     static_assert(ST != kF32, "16-bit fields");
-    constexpr int MODE = kFwd;
     using T = typename Stor<ST>::T;
     using CT = std::conditional_t<CQ, uint16_t, float>;
-    constexpr int TX = 64 * VX;
+    constexpr int VX = k2dVX, TX = 64 * VX;
     const int lane = threadIdx.x & 63;
     const int xb = tx * TX;
     const int x0 = xb + lane * VX;
@@ -283,7 +283,7 @@ __device__ __forceinline__ void step2d_tile(const StepArgs &a, int tx, int tz,
         // the previous row's stores go out after the wait for this row's
         // data and just before the next prefetch
         __builtin_amdgcn_sched_barrier(0);
-        flush<T, VX, MODE, false>(out);
+        flush<T, VX, kFwd, false>(out);
         la = ld_cur(z + 5);
         pv = ld_prev(z + 1);
         cv = ld_c(z + 1);
@@ -294,8 +294,7 @@ __device__ __forceinline__ void step2d_tile(const StepArgs &a, int tx, int tz,
         for (int v = 0; v < VX; ++v) rw[4 + lane * VX + v] = q[4][v];
         if (hlane) rw[hslot] = hc;
         __syncthreads();
-        const float gzz = gzp;
-        float nw[VX], lp[VX], G[VX];
+        float nw[VX], G[VX];
 #pragma unroll
         for (int v = 0; v < VX; ++v) {
             const int li = 4 + lane * VX + v;
@@ -304,24 +303,24 @@ __device__ __forceinline__ void step2d_tile(const StepArgs &a, int tx, int tz,
             const float lz = stencil_taps(q[0][v], q[1][v], q[2][v], q[3][v], q[5][v], q[6][v],
                                           q[7][v], q[8][v]);
             const float lap = fmaf(2.0f * kA0, q[4][v], lz + lx);
-            G[v] = gzz * gxv[v];
+            G[v] = gzp * gxv[v];
             nw[v] = update<ST>(G[v], q[4][v], cc[v], lap, pc[v], h);
-            lp[v] = lap;
         }
-        finish_cells<ST, VX, MODE, false, false>(a, h, z, 0, x0, lane_in, (size_t)z * px, (uint32_t)x0, nw,
-                                                 lp, pc, cc, G, inj, bmax, out);
+        // (the forward step stores no history value: q[4] stands in for it)
+        finish_cells<ST, VX, kFwd, false, false>(a, h, z, 0, x0, lane_in, (size_t)z * px, (uint32_t)x0, nw,
+                                                 q[4], pc, cc, G, inj, bmax, out);
 #pragma unroll
         for (int k = 0; k < 8; ++k)
 #pragma unroll
             for (int v = 0; v < VX; ++v) q[k][v] = q[k + 1][v];
     }
-    flush<T, VX, MODE, false>(out);
+    flush<T, VX, kFwd, false>(out);
 }
 
-template <int ST, int VX, bool CQ>
+template <int ST, bool CQ>
 __global__ __launch_bounds__(64) void k_step2d(StepArgs a)
 {
-    __shared__ float row[2][64 * VX + 8];
+    __shared__ float row[2][64 * k2dVX + 8];
     const int nb = a.tiles_x * a.tiles_z;
     const int t = xcd_tile(blockIdx.x, nb);
     const int tx = t % a.tiles_x, tz = t / a.tiles_x;
@@ -329,7 +328,7 @@ __global__ __launch_bounds__(64) void k_step2d(StepArgs a)
     if (a.n + 1 < a.nt) inj = a.amp * a.wavelet[a.n + 1];
     const HalfCtx h = half_prologue<ST>(a, inj, blockIdx.x == 0);
     float bmax = 0.0f;
-    step2d_tile<ST, VX, CQ>(a, tx, tz, row, h, inj, bmax);
+    step2d_tile<ST, CQ>(a, tx, tz, row, h, inj, bmax);
     block_max_to<64>(max_slot(a.meta, (int)((a.n + 1) & 3)), bmax * h.sn, nullptr);
 }
 
@@ -1515,7 +1514,7 @@ static void launch2d(const StepArgs &a, int nb, hipStream_t s)
         if (a.vx == 1) hipLaunchKernelGGL((k_step2d_block<ST, 1, MODE, CQ>), dim3(nb), dim3(256), 0, s, a);
         else if (a.vx == 2) hipLaunchKernelGGL((k_step2d_block<ST, 2, MODE, CQ>), dim3(nb), dim3(256), 0, s, a);
         else if (a.vx == 4) hipLaunchKernelGGL((k_step2d_block<ST, 4, MODE, CQ>), dim3(nb), dim3(256), 0, s, a);
-        else hipLaunchKernelGGL((k_step2d<ST, 2, CQ>), dim3(nb), dim3(64), 0, s, a);
+        else hipLaunchKernelGGL((k_step2d<ST, CQ>), dim3(nb), dim3(64), 0, s, a);
     }
 }
 
