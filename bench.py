@@ -293,7 +293,7 @@ def summarize_serving_trace(kt_dir: str, requests: int):
     """GPU busy time of the batched serving run from a rocprofv3 kernel trace
     (`--kernel-trace -f csv`) of `bench.py --legs serve`: the union of kernel
     intervals between the two markers, the largest kernels and the gaps.
-    Writes profiles/k_step2d_batch_serving.md."""
+    Writes profiles/serving_kernels.md."""
     import collections
     import csv
     import glob
@@ -340,7 +340,7 @@ def summarize_serving_trace(kt_dir: str, requests: int):
         lines.append(f"| {n} | {cnt[n]} | {t / 1e9:.3f} | {t / cnt[n] / 1e3:.1f} |")
     lines += ["", f"Summary written by `python bench.py --summarize-serving-trace {kt_dir} "
                   f"--serve-requests {requests}`.", ""]
-    with open(os.path.join(ROOT, "profiles", "k_step2d_batch_serving.md"), "w") as fh:
+    with open(os.path.join(ROOT, "profiles", "serving_kernels.md"), "w") as fh:
         fh.write("\n".join(lines))
     print(json.dumps(dict(window_s=span / 1e9, busy_frac=busy / span, launches=len(win))))
 
@@ -394,8 +394,8 @@ def serve_leg(n_requests: int = 1000, seed: int = 50, n_sub: int = 500, sub_frac
                 log(f"[bench] serve {tag}: {done}/{total} shots done")
         # "batched": the earliest-arrived resident shot and then the shots
         # with the least remaining work advance, enough of them to give each
-        # launch 20 M cells per step (fields that fit the Infinity Cache),
-        # the others wait resident
+        # call 20 M cells (the library cuts them into launches), the others
+        # wait resident
         for name, batched, slots, policy in (("batched", True, 64, "srpt_oldest"),
                                              ("sequential", False, 1, "all")):
             torch.cuda.synchronize()
@@ -801,7 +801,7 @@ def main():
                     help="write profiles/ summaries from rocprofv3 CSV output (host only)")
     ap.add_argument("--summarize-serving-trace", metavar="KT_DIR",
                     help="GPU busy time of the batched serving run from a rocprofv3 kernel trace "
-                         "of --legs serve (writes profiles/k_step2d_batch_serving.md)")
+                         "of --legs serve (writes profiles/serving_kernels.md)")
     ap.add_argument("--oracle-table", action="store_true",
                     help="only the FP64 oracle's rate on samples of every configuration (host only)")
     args = ap.parse_args()

@@ -6,7 +6,8 @@
  * (z, y, x), by explicit finite differences: one time step is the sequence
  * of Listing 3 (source addition to P, second derivatives along each axis,
  * time update to Pnew, rotation of Pold/P/Pnew), fused here into one kernel
- * per step.  Readings of what the paper leaves open:
+ * per step, or per several steps in 2D with FP32 fields.  Readings of what the
+ * paper leaves open:
  *   - second derivatives: 8th-order central weights (radius R = 4)
  *     a = (-205/72, 8/5, -1/5, 8/315, -1/560); taps outside the grid read 0;
  *   - one grid spacing dh on every axis (the paper's single dh); the
@@ -285,9 +286,9 @@ fd_status fd_rtm_image(const fd_model *model, const fd_shot *shot, const float *
 
 /* Several shots on one model at once (the shots of one survey: a
  * gradient or an image sums over them).  `count` entries in each array;
- * all shots share nt.  In 2D with FP32 storage the shots share every launch
- * (groups of FD_BATCH_MAX), which keeps the device full on grids too small
- * to fill it alone; otherwise
+ * all shots share nt.  In 2D with FP32 storage the shots of a group (at most
+ * FD_BATCH_MAX, fewer on large grids) share every launch, which keeps the
+ * device full on grids too small to fill it alone; otherwise
  * the shots run one after another.  Per shot, the results are those of the
  * single-shot call, bit for bit:
  *   fd_run_shots               = fd_run_shot on each (states[i], shots[i],

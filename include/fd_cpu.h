@@ -16,6 +16,8 @@
  *     256-byte aligned as in fd.h);
  *   - `stream` arguments are ignored and every call returns when its work is
  *     done;
+ *   - fd_sizes.state is two time levels on every grid (each step is one pass
+ *     over the grid, so there is no second pair);
  *   - built: fd_query_bytes, fd_create_model / fd_destroy_model,
  *     fd_create_state / fd_destroy_state, fd_begin_shot, fd_step,
  *     fd_run_shot (without checkpoints), fd_run_shots, fd_get_wavefield,

@@ -60,7 +60,13 @@ __device__ __forceinline__ float axis_d2_shared(float s4, float s3, float s2, fl
     return fmaf(kC34, u, fmaf(kA4, s4, fmaf(kA3, s3, fmaf(kA2, s2, kA1 * s1))));
 }
 
-// axis_d2 at the N centres in[4 .. 4 + N) of a run of N + 8 cells.
+// axis_d2 at the N centres in[4 .. 4 + N) of a run of N + 8 cells, from
+// differences that neighbouring centres share.  u - u[-k] is the exact negative
+// of u[-k] - u unless both are zero (+0 either way), so the values are those
+// of axis_d2, and the bits too but for the sign of a zero, which can differ
+// where u is +0 beside a -0.  It goes no further: with u = +0 the update forms
+// fma(c, lap, u - G prev), and both u - G prev = +0 and a nonzero one give the
+// same bits for either zero lap; likewise fma(z, lap, g) for a sum begun at +0.
 template <int N>
 __device__ __forceinline__ void axis_d2_run(const float (&in)[N + 8], float (&out)[N])
 {

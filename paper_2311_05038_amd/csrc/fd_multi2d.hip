@@ -18,11 +18,12 @@
 // 8 S cells, so S steps cost (ext tile minus the skipped rows) / (inner tile)
 // of the work: 1.56 for S = 4 on 128 x 128.
 //
-// The work is VALU-bound (30 instructions per cell and step): the differences
-// of neighbouring cells that the second difference needs twice, u[i+1] - u[i]
-// and u[i+2] - u[i], are formed once per run of cells and subtracted, which
-// gives the bits of axis_d2 (negation is exact) with 1.25 instructions less
-// per axis and cell.
+// The forward step is VALU-bound (by the counters 34 vector instructions per
+// computed cell and step, which take 82% of a launch's time on 2048 x 4096 and
+// 66% on 1024^2; the adjoint's 43%, its history and FP64 sum move at 4.5 TB/s):
+// the differences of neighbouring cells that the second difference needs
+// twice, u[i+1] - u[i] and u[i+2] - u[i], are formed once per run of cells and
+// subtracted, 1.25 instructions less per axis and cell than in axis_d2.
 //
 // A block walks over its tiles: the next tile's P is copied straight into the
 // LDS buffer that the last step of the present one no longer writes, and
@@ -30,7 +31,7 @@
 // a block's first tile waits for its loads.
 //
 // Per cell the operations and their order are those of the single step
-// kernels: the results are the same bits.
+// kernels in 2D: the results are the same bits.
 #include <algorithm>
 
 #include "fd_device.hpp"
@@ -384,8 +385,10 @@ __global__ __launch_bounds__(TXL *NZ, WPS) void k_multi2d(const MultiBatch<N> b)
 // --------------------------------------------------------------------------
 namespace {
 
-// The tile shapes, with what a launch of them costs in us (least squares over
-// 1 to 10 steps on 15 grids and surveys of 200 x 170 to 12 x 700 x 1500; 7% rms):
+// The tile shapes, with what a launch of them costs in us (least squares of the
+// relative error over 1 to 10 steps on 17 grids and surveys of 200 x 170 to 12 x
+// 700 x 1500, 8% rms, 14% for the 128 x 128 recompute and adjoint; the timed
+// launches are in profiles/multi_step_costs.csv):
 // per round of blocks and tile `tile` + `step` for every step, in proportion
 // to the rows that still take part, + `odd` from the second round on when an
 // odd number of steps leaves no buffer to copy the next tile into.  Rows:

@@ -31,11 +31,12 @@ struct ShortPlan {
 // 333 x 289 61.5 / 58).  Where the tiles reach past the last row they cover
 // more than the streaming kernel's 8-row tiles and idle threads still take
 // their place: 5% more is outweighed; more than that only if all blocks run in
-// one round (100 x 8 x 1000: 800 blocks 8.0 us against 10.6; 1500 x 8 x 300:
-// 3750 blocks 20.1 against 16.1), or nearly so with up to 18% (100 x 65 x 1000:
-// 4000 blocks 31.4 us against 32.7; 100 x 49 x 4000: 6300 blocks 81 against
-// 67).  Share of rows and blocks at which it lost: 1/2 and 2000 0.77, 3/4 and
-// 1600 0.90, 5/6 and 4725 0.90 (time of the streaming kernel over its own).
+// one round (100 x 8 x 1000, 800 blocks: a gradient 399 us against 485; 1500 x
+// 8 x 300, 3750 blocks: 20.1 us against 16.1), or nearly so with up to 18% (100
+// x 65 x 1000, 4000 blocks: a gradient 1634 us against 1767; 100 x 49 x 4000,
+// 6300 blocks: 81 us against 67).  Share of rows in use and blocks at which it
+// lost: 1/2 and 2000 0.77, 3/4 and 1600 0.90, 5/6 and 4725 0.90 (time of the
+// streaming kernel over its own).
 //
 // Beyond 22 M cells, with accesses that bypass the caches, it stays ahead for
 // the adjoint step (384^3 239 against 260 us, 512^3 560 against 562), tiles
@@ -47,7 +48,7 @@ struct ShortPlan {
 //
 // With 16-bit fields it pays up to 3 M padded cells (BF16, streaming / short:
 // 48^3 9.7 / 6.4 us, 66 x 480 x 49 16.9 / 10.0, 96 x 120 x 152 14.3 / 11.8; with
-// tiles past the last row 100 x 8 x 1000 10.7 / 8.0, 1000 x 4 x 500 16.9 /
+// tiles past the last row 100 x 8 x 1000 11.7 / 8.7, 1000 x 4 x 500 16.9 /
 // 21.9); the streaming kernel's fewer, longer blocks read the magnitude words
 // and fold a maximum less often, and larger grids keep it.
 inline ShortPlan short_plan(int64_t nz, int64_t ny, int64_t nx, int64_t px, bool f32, bool adjoint, int64_t tx,
