@@ -22,6 +22,8 @@ SURVEYS = [
     (2, 999, 2001, 13, 13),     # 96 x 96 (4), 128 x 128 (2)
     (8, 1023, 1023, 17, 17),    # 96 x 96 (6), 128 x 96 (5), 128 x 128 (4)
     (7, 1447, 1449, 9, 9),      # 14.9 M cells: groups of 3 and 4 shots
+    (1, 2000, 2000, 11, 5),     # lone adjoint steps split off, launches of several after them
+    (2, 700, 1200, 7, 2),       # two steps a segment, a lone one in the first
     (17, 901, 1025, 7, 4),      # more shots than a launch holds, groups of fewer
 ]
 
