@@ -101,7 +101,8 @@ MultiPlan plan_multi(const fdk::MultiGrid *grids, int count, int64_t run, int mo
     for (int k = 1; k <= fdk::kMultiSteps; ++k) {
         if (fdk::multi2d_shape(grids, count, k, mode, &us[k]) < 0) us[k] = 1e300;
         // beyond the cache a launch of few steps is bound by its 24 bytes a
-        // cell (3000 x 5000: 1 + 2 steps 131 us, three single steps 115)
+        // cell (a shot of three steps on 3000 x 5000: 162 us as 2 + 1, 145 as
+        // single steps)
         if (cells > kGroupCells) us[k] = std::max(us[k], 2.5 + cells * 3.8e-6);
     }
     if (mode == fdk::kAdj) us[1] = single_adjoint_us(covered);
